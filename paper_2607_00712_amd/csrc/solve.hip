@@ -23,11 +23,11 @@
 //   the wave; the off-diagonal pieces are 32 x 32 x 32 MFMA products.
 // Triangular solves in block LDL^T form over 256-blocks (details below): the
 //   inverses X_I of the 256 x 256 diagonal blocks of L and P_I = X_I^T X_I,
-//   Lh = L diag(X_I) below the 256-block diagonal (its transpose mirrored into
-//   the upper part), then one right-looking rank-256 GEMM launch per block for
-//   the forward and for the backward sweep, with no diagonal work in them.
-// Every product is fp32 MFMA (v_mfma_f32_32x32x2f32); the sweeps' GEMM stages
-// its operands HBM -> LDS with direct buffer loads in a 4-deep ring.
+//   Lh = L diag(X_I) below the 256-block diagonal, then one right-looking
+//   rank-256 GEMM launch per block for the forward and for the backward sweep,
+//   with no diagonal work in them.
+// The sweeps' products run on the bf16 matrix cores with every fp32 operand cut
+// into three bf16 parts (below); the others are fp32 MFMA.
 // Several layers at once (the end of warmup solves every layer): every kernel
 // takes its layer from the last grid dimension and offsets its workspace
 // pointers by the layers' workspace stride (dW by its own stride), so one
@@ -324,8 +324,8 @@ __device__ __forceinline__ void tri_index(int t, int& ti, int& tj) {
 }
 
 // L = lower(G) + lambda I with zeros above the diagonal up to the end of the
-// row's 256-block (the part above the 256-block diagonal is never read before
-// the mirror of Lh overwrites it), status = 0. Row blockIdx.x, four columns per
+// row's 256-block (the part above the 256-block diagonal is never read),
+// status = 0. Row blockIdx.x, four columns per
 // thread (n is a multiple of 4); only G's lower triangle is read.
 __global__ void solve_init_kernel(const float* G, float* L, int n, float lambda, int* status, int64_t ws) {
   G = at_layer(G, ws, blockIdx.y);
@@ -618,8 +618,7 @@ __global__ __launch_bounds__(kThreads) void chol_step_kernel(float* L, float* Di
 // Both unit-triangular sweeps are right-looking rank-256 GEMM updates with no
 // diagonal work, one launch per block: Y_r -= Lh_rI Y_I (r > I) and
 // dW_I -= Lh_JI^T dW_J (I < J). Lh overwrites the strictly-below-256-block part
-// of L and its transpose is mirrored into the (otherwise zero) upper part, so
-// that every GEMM operand is read as rows of a row-major matrix.
+// of L.
 constexpr int kBb = 256;  // block size of the triangular sweeps
 constexpr int kKc = 16;   // k rows per LDS chunk of the GEMM
 
@@ -686,26 +685,6 @@ __global__ __launch_bounds__(kThreads) void inv256_kernel(const float* L, const 
   }
 }
 
-// Upper part of L from Lh: U[c][r] = L[r][c] for every (r, c) whose 256-block
-// row is below its 256-block column. One 64 x 64 tile per workgroup.
-__global__ __launch_bounds__(kThreads) void mirror_kernel(float* L, int n, int64_t ws) {
-  __shared__ Tile T;
-  L = at_layer(L, ws, blockIdx.y);
-  const int nblk = (n + kNb - 1) / kNb;
-  const int tr = blockIdx.x / nblk, tc = blockIdx.x % nblk;
-  if (tr / 4 <= tc / 4) return;
-  const int rr = min(kNb, n - tr * kNb), rc = min(kNb, n - tc * kNb);
-  load_tile(T, L + (int64_t)tr * kNb * n + (int64_t)tc * kNb, n, rr, rc);
-  __syncthreads();
-  float* dst = L + (int64_t)tc * kNb * n + (int64_t)tr * kNb;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = threadIdx.x + q * kThreads;
-    const int r = e >> 4, c = (e & 15) * 4;
-    if (r < rc && c < rr) *(f32x4*)(dst + (int64_t)r * n + c) = f32x4{T[c][r], T[c + 1][r], T[c + 2][r], T[c + 3][r]};
-  }
-}
-
 // C(m, n) = [C(m, n) -] sum_k A(m, k) B(k, n) for m < M, n < N, in fp32 MFMA.
 // B(k, n) = B[k * ldb + n]. A(m, k) = A[k * lda + m] (k-major), or
 // A[m * lda + k] for the m-major instantiation. One launch runs up to two jobs
@@ -720,10 +699,7 @@ struct GemmJob {
   int M;
   int64_t lda, ldc;
   int sub;                    // 1: C -= A B, 0: C = A B
-  const float* Cin = nullptr;  // with sub: read the minuend here instead of C (same ldc)
-  int64_t la = 0, lc = 0;      // bytes per layer (blockIdx.z) of A and of C / Cin
-  const float* B = nullptr;    // this job's own B operand and depth (gemm_ring_kernel only);
-  int K = 0;                   // null / 0: the shared B and K below
+  int64_t la = 0, lc = 0;  // bytes per layer (blockIdx.z) of A and of C
 };
 struct GemmArgs {
   GemmJob job[2];
@@ -943,215 +919,260 @@ __global__ __launch_bounds__(kThreads) void eps_final_kernel(const double* part,
 
 namespace {
 
-// ---------------------------------------------------------------- ring GEMM
-// The sweeps' GEMM (both operands k-major: A(m, k) = A[k * lda + m]) with the
-// operands staged HBM -> LDS by buffer loads straight into LDS, in a ring of 4
-// stages of 16 k-rows, 3 stages ahead of the MFMAs. A stage side holds 16 rows
-// of the tile's TM (or TN) columns, 16-byte chunk c of row k stored at chunk
-// c ^ 8 (k & 1): the two k-rows read by one MFMA operand sit 32 banks apart.
-// The buffer descriptor of a side ends at the last valid element of the job,
-// so k-rows past K read as zero; columns past M or N read finite neighbouring
-// data that only reaches outputs that are not stored.
-constexpr int kRing = 4;
-
-template <int N>
-__device__ __forceinline__ void vm_wait() {
-  static_assert(N >= 0 && N <= 63, "vmcnt range");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory");
-}
-
-template <int T>
-__device__ __forceinline__ void ring_side(const float* src, int64_t ld, int k0, int kend, int c0, int cend, char* dst,
-                                          int wave, int lane) {
-  int64_t nrec = ((int64_t)(kend - k0 - 1) * ld + (cend - c0)) * 4;
-  if (nrec < 0) nrec = 0;
-  if (nrec > 0x7fffffff) nrec = 0x7fffffff;
-  const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(src + (int64_t)k0 * ld + c0), 0, (int)nrec, 0x00020000);
-  constexpr int kChunks = T / 4;  // 16-byte chunks per row
-#pragma unroll
-  for (int q = 0; q < kKc * T * 4 / (kThreads * 16); ++q) {
-    const int slot = (q * 4 + wave) * 64 + lane;
-    const int row = slot / kChunks;
-    const int c = (slot % kChunks) ^ ((row & 1) << 3);
-    const int voff = (int)((row * ld + c * 4) * 4);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (ISPA_LDS void*)(dst + (q * 4 + wave) * 1024), 16, voff, 0, 0, 0);
-  }
-}
-
-template <int QM, int QN>
-struct RingRegs {
-  float a[2][QM], b[2][QN];
-};
-
-// LDS reads of k-row pair KK of stage buffer BUF into register set S
-template <int IMMA, int IMMB, int QM, int QN>
-__device__ __forceinline__ void ring_issue(const uint32_t (&oa)[QM], const uint32_t (&ob)[QN], float (&a)[QM],
-                                           float (&b)[QN]) {
-#pragma unroll
-  for (int i = 0; i < QM; ++i) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(a[i]) : "v"(oa[i]), "i"(IMMA));
-#pragma unroll
-  for (int j = 0; j < QN; ++j) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(b[j]) : "v"(ob[j]), "i"(IMMB));
-}
-
-// at most N LDS operations outstanding: the reads into a, b have landed
-template <int N, int QM, int QN>
-__device__ __forceinline__ void ring_wait(float (&a)[QM], float (&b)[QN]) {
-  static_assert(N >= 0 && N <= 15 && ((QM == 2 && QN == 2) || (QM == 1 && QN == 1)), "shape");
-  if constexpr (QM == 2) {
-    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a[0]), "+v"(a[1]), "+v"(b[0]), "+v"(b[1]) : "i"(N));
-  } else {
-    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a[0]), "+v"(b[0]) : "i"(N));
-  }
-}
-
-template <int BUF, int KK, int TM, int TN, int QM, int QN>
-__device__ __forceinline__ void ring_ksteps(const uint32_t (&oa)[QM], const uint32_t (&ob)[QN], RingRegs<QM, QN>& r,
-                                            f32x16 (&acc)[QM][QN]) {
-  constexpr int kStage = kKc * (TM + TN) * 4;
-  constexpr int cur = (KK / 2) & 1;
-  if constexpr (KK + 2 < kKc) {
-    ring_issue<BUF * kStage + (KK + 2) * TM * 4, BUF * kStage + (KK + 2) * TN * 4, QM, QN>(oa, ob, r.a[cur ^ 1],
-                                                                                           r.b[cur ^ 1]);
-    ring_wait<QM + QN, QM, QN>(r.a[cur], r.b[cur]);
-  } else {
-    ring_wait<0, QM, QN>(r.a[cur], r.b[cur]);
-  }
-#pragma unroll
-  for (int i = 0; i < QM; ++i)
-#pragma unroll
-    for (int j = 0; j < QN; ++j) acc[i][j] = mfma_f32(r.a[cur][i], r.b[cur][j], acc[i][j]);
-  if constexpr (KK + 2 < kKc) ring_ksteps<BUF, KK + 2, TM, TN, QM, QN>(oa, ob, r, acc);
-}
-
-struct RingTile {
+// ---------------------------------------------------------------- split GEMM
+// The sweeps' GEMM, C(m, n) = [Cin(m, n) -] sum_k A(m, k) B(k, n), fp32 in and
+// out, on the bf16 matrix cores: every operand value is cut into three bf16
+// parts x = x0 + x1 + x2 (each the rounding of what is left: 3 x 8 significand
+// bits hold fp32's 24 exactly), and of the nine products of two values the six
+// with i + j <= 2 are summed in fp32; the three left out are below 2^-25 of the
+// product, less than one fp32 rounding. Six bf16 MFMAs of 32x32x16 take 192
+// cycles where the fp32 form takes eight 32x32x2 of 64, and round the sum a
+// third as often (dW against 64 bits: 7.6e-7 / 1.5e-6 at 1536 / 5120, 8.0e-7 /
+// 1.5e-6 with fp32 MFMAs).
+//
+// Tile T x T (T = 64 Q), 4 waves of 32 Q x 32 Q, two or three workgroups on a CU.
+// A thread holds one chunk of 8 k of one row of A and of B, loaded two stages
+// ahead into registers and cut and written to LDS one stage ahead (two buffers,
+// one barrier per stage): the cut is done once per workgroup, not per wave, and
+// three planes of rows with k contiguous make an operand one ds_read_b128 per
+// plane. B(k, n) = B[k ldb + n]; A(m, k) = A[m lda + k] (A_KM = false) or A[k lda
+// + m] (true), so the lower triangle of L serves both sweeps. The minuend's
+// loads are issued before the last stage's products (30 layers of 1536: the
+// first forward launch 275 us against 377 with the loads at the end, 395 with
+// the fp32 kernel before). What bounds it: 0.75 of the time of a launch is loads,
+// cuts and barriers that two workgroups per CU do not hide (132 TFLOP/s there,
+// 145 at one layer of 5120, against 92-110 before).
+//
+// The descriptor of a side ends at its last valid element, so k past K reads
+// zero where k is the source's row and is masked where k is the column; rows and
+// columns past M or N only reach outputs that are not stored. The order of an
+// output's sum does not depend on the tile size: both give the same bits. An
+// infinite value, or one that rounds to an infinite bf16, gives NaN.
+struct SplitJob {
   const float* A;
+  float* C;
+  const float* Cin;  // minuend (null: C = A B)
   const float* B;
-  int64_t lda, ldb;
-  int M, N, K, m0, n0, steps, wave, lane;
+  int M, K;
+  int64_t lda, ldc;
+  int64_t la, lc;  // bytes per layer of A and of C / Cin
+};
+struct SplitArgs {
+  SplitJob job[2];
+  int n_jobs, N, layers;
+  int64_t ldb, lb;  // lb: bytes per layer of B
 };
 
-template <int TM, int TN>
-__device__ __forceinline__ void ring_load(const RingTile& t, char* smem, int s) {
-  constexpr int kStage = kKc * (TM + TN) * 4;
-  char* d = smem + (s % kRing) * kStage;
-  const int k0 = s * kKc;
-  ring_side<TM>(t.A, t.lda, k0, t.K, t.m0, t.M, d, t.wave, t.lane);
-  ring_side<TN>(t.B, t.ldb, k0, t.K, t.n0, t.N, d + kKc * TM * 4, t.wave, t.lane);
+typedef unsigned int u32;
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// x[0..7] cut into three bf16 chunks of 8
+__device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&p)[3]) {
+  // (-1, 0) and (0, -1) as packed bf16, kept out of the compiler's sight: as an
+  // inline constant of a packed operand -1.0 is taken for the wrong half
+  u32 lo = 0x0000bf80u, hi = 0xbf800000u;
+  asm("" : "+s"(lo), "+s"(hi));
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float a = x[2 * j], b = x[2 * j + 1];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const bf16x2 w = __builtin_convertvector((f32x2{a, b}), bf16x2);
+      p[q][j] = __builtin_bit_cast(u32, w);
+      if (q < 2) {  // what the part left: one multiply-add with the pair, exact
+        a = __builtin_amdgcn_fdot2_f32_bf16(w, __builtin_bit_cast(bf16x2, lo), a, false);
+        b = __builtin_amdgcn_fdot2_f32_bf16(w, __builtin_bit_cast(bf16x2, hi), b, false);
+      }
+    }
+  }
 }
 
-// stage s from ring buffer BUF = s % 4: loads of stage s + 3, the MFMAs of s,
-// then wait for stage s + 1 (direct loads retire in order) and synchronise
-template <int BUF, int TM, int TN, int QM, int QN>
-__device__ __forceinline__ void ring_stage(const RingTile& t, char* smem, const uint32_t (&oa)[QM],
-                                           const uint32_t (&ob)[QN], f32x16 (&acc)[QM][QN], int s) {
-  constexpr int kLoads = (TM + TN) / 64;  // direct loads per thread per stage
-  if (s + 3 < t.steps) ring_load<TM, TN>(t, smem, s + 3);
-  RingRegs<QM, QN> r;
-  ring_issue<BUF * kKc * (TM + TN) * 4, BUF * kKc * (TM + TN) * 4, QM, QN>(oa, ob, r.a[0], r.b[0]);
-  ring_ksteps<BUF, 0, TM, TN, QM, QN>(oa, ob, r, acc);
-  const int younger = t.steps - (s + 2);
-  if (younger >= 2) {
-    vm_wait<2 * kLoads>();
-  } else if (younger == 1) {
-    vm_wait<kLoads>();
-  } else {
-    vm_wait<0>();
-  }
-  // the direct loads of stage s + 1 have landed (vmcnt above) and every LDS
-  // read of this wave has completed (lgkmcnt(0) in the last k-step): a bare barrier
-  // suffices, where a fenced one would also wait for the younger stages
-  __builtin_amdgcn_s_barrier();
-}
+// One side of the tile: T rows of the LDS planes (the m or n index), KS k; every
+// thread holds one chunk of 8 k of one row. KM: k is the row of the source,
+// else the column.
+template <int T, bool KM>
+struct SplitSide {
+  static constexpr int kChunks = kThreads / T;  // per row
+  static constexpr int kKs = 8 * kChunks;       // k per stage
+  static constexpr int kBytes = T * kKs * 2 * 3;
+  __amdgpu_buffer_rsrc_t rs;
+  int voff[KM ? 8 : 1], step, k_first, dst;
+  float v[8];
 
-template <int WM, int WN, int QM, int QN>
-__global__ __launch_bounds__(kThreads) void gemm_ring_kernel(GemmArgs g) {
-  constexpr int TM = WM * QM * 32, TN = WN * QN * 32;
-  constexpr int kLoads = (TM + TN) / 64;
-  static_assert(WM * WN == kThreads / 64, "4 waves");
-  __shared__ __attribute__((aligned(1024))) char smem[kRing * kKc * (TM + TN) * 4];
-
-  const int tiles_n = (g.N + TN - 1) / TN;
-  const int m_tiles0 = (g.job[0].M + TM - 1) / TM;
-  int tt = blockIdx.x;
-  const bool second = tt >= m_tiles0 * tiles_n;
-  if (second) {
-    if (g.n_jobs < 2) return;
-    tt -= m_tiles0 * tiles_n;
+  // byte of chunk c of row r in a plane: a 16-lane group of an operand read
+  // (16 rows, one chunk) covers all banks once
+  static __device__ __forceinline__ int slot(int r, int c) {
+    return r * kKs * 2 + ((c ^ (kChunks == 4 ? (r >> 2) & 3 : (r >> 3) & 1)) << 4);
   }
-  RingTile t;
-  t.A = second ? g.job[1].A : g.job[0].A;
-  float* C = second ? g.job[1].C : g.job[0].C;
-  t.M = second ? g.job[1].M : g.job[0].M;
-  t.lda = second ? g.job[1].lda : g.job[0].lda;
-  const int64_t ldc = second ? g.job[1].ldc : g.job[0].ldc;
-  const int sub = second ? g.job[1].sub : g.job[0].sub;
-  const float* Cin = second ? g.job[1].Cin : g.job[0].Cin;
-  if (Cin == nullptr) Cin = C;
-  t.m0 = (tt / tiles_n) * TM;
-  t.n0 = (tt % tiles_n) * TN;
-  if (t.m0 >= t.M) return;
+  __device__ __forceinline__ void init(const float* src, int64_t ld, int i0, int iend, int K) {
+    const int t = threadIdx.x;
+    const float* base = KM ? src + i0 : src + (int64_t)i0 * ld;
+    int64_t nrec = (KM ? (int64_t)(K - 1) * ld + (iend - i0) : (int64_t)(iend - i0 - 1) * ld + K) * 4;
+    if (nrec > 0x7fffffff) nrec = 0x7fffffff;
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)nrec, 0x00020000);
+    const int ld4 = (int)(ld * 4);
+    const int row = KM ? t % T : t / kChunks, chunk = KM ? t / T : t % kChunks;
+    k_first = chunk * 8;
+    dst = slot(row, chunk);
+    if (KM) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) voff[k % (KM ? 8 : 1)] = (k_first + k) * ld4 + row * 4;
+      step = kKs * ld4;
+    } else {
+      voff[0] = row * ld4 + k_first * 4;
+      step = kKs * 4;
+    }
+  }
+  __device__ __forceinline__ void load(int s) {
+    if (KM) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        v[k] = __builtin_bit_cast(float, (u32)__builtin_amdgcn_raw_buffer_load_b32(rs, voff[k % (KM ? 8 : 1)], s * step, 0));
+    } else {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const f32x4 w = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff[0] + q * 16, s * step, 0));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[4 * q + j] = w[j];
+      }
+    }
+  }
+  // k >= K of a stage reads the neighbouring columns of its row: zero them
+  __device__ __forceinline__ void mask(int k0, int K) {
+    if (KM) return;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (k0 + k_first + k >= K) v[k] = 0.f;
+  }
+  __device__ __forceinline__ void put(char* lds) const {
+    u32x4 p[3];
+    split8(v, p);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *(u32x4*)(lds + q * (kBytes / 3) + dst) = p[q];
+  }
+};
+
+template <int Q, bool A_KM>
+__global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(SplitArgs g) {
+  constexpr int T = 64 * Q;
+  using SideA = SplitSide<T, A_KM>;
+  using SideB = SplitSide<T, true>;
+  constexpr int kKs = SideA::kKs, kSide = SideA::kBytes;
+  __shared__ __attribute__((aligned(1024))) char smem[2][2 * kSide];
+  // consecutive tiles (n fastest, then m, job, layer) on one XCD
+  const int tiles_n = (g.N + T - 1) / T;
+  const int t0 = (g.job[0].M + T - 1) / T * tiles_n;
+  const int t1 = g.n_jobs > 1 ? (g.job[1].M + T - 1) / T * tiles_n : 0;
+  const int total = (t0 + t1) * g.layers;
+  const int idx = (int)(blockIdx.x & 7) * ((int)gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  if (idx >= total) return;
+  const int layer = idx / (t0 + t1);
+  int t = idx - layer * (t0 + t1);
+  const SplitJob& jb = t < t0 ? g.job[0] : g.job[1];
+  if (t >= t0) t -= t0;
+  const int m0 = t / tiles_n * T, n0 = t % tiles_n * T;
+  const int M = jb.M, N = g.N, K = jb.K;
+  SideA sa;
+  SideB sb;
+  sa.init(at_layer(jb.A, jb.la, layer), jb.lda, m0, M, K);
+  sb.init(at_layer(jb.B, g.lb, layer), g.ldb, n0, N, K);
+
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l32 = lane & 31, h = lane >> 5;
+  const int wm0 = (wave >> 1) * 32 * Q, wn0 = (wave & 1) * 32 * Q;
+
+  f32x16 acc[Q][Q];
+#pragma unroll
+  for (int i = 0; i < Q; ++i)
+#pragma unroll
+    for (int j = 0; j < Q; ++j) acc[i][j] = f32x16{};
+
+  float* C = at_layer(jb.C, jb.lc, layer);
+  const float* Cin = at_layer(jb.Cin, jb.lc, layer);
+
+  // the minuend through a descriptor that ends at the job's last element: rows
+  // past M read zero, columns past N neighbours that are not stored
+  float cin[Q][Q][16];
+  __amdgpu_buffer_rsrc_t rc;
+  int coff;
   {
-    const int layer = blockIdx.z;
-    const int64_t lc = second ? g.job[1].lc : g.job[0].lc;
-    t.A = at_layer(t.A, second ? g.job[1].la : g.job[0].la, layer);
-    C = at_layer(C, lc, layer);
-    Cin = at_layer(Cin, lc, layer);
+    int64_t nrec = jb.Cin != nullptr ? ((int64_t)(M - m0 - 1) * jb.ldc + (N - n0)) * 4 : 0;
+    if (nrec > 0x7fffffff) nrec = 0x7fffffff;
+    rc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Cin + (int64_t)m0 * jb.ldc + n0), 0, (int)nrec, 0x00020000);
+    coff = (int)(((wm0 + 4 * h) * jb.ldc + wn0 + l32) * 4);
   }
-  {
-    const GemmJob& jb = second ? g.job[1] : g.job[0];
-    t.B = at_layer(jb.B ? jb.B : g.B, g.lb, blockIdx.z);
-    t.K = jb.K ? jb.K : g.K;
+  const int ldc4 = (int)(jb.ldc * 4);
+
+  const int steps = (K + kKs - 1) / kKs;
+  sa.load(0);
+  sb.load(0);
+  if (kKs > K) sa.mask(0, K);
+  sa.put(smem[0]);
+  sb.put(smem[0] + kSide);
+  if (steps > 1) {
+    sa.load(1);
+    sb.load(1);
   }
-  t.ldb = g.ldb;
-  t.N = g.N;
-  t.steps = (t.K + kKc - 1) / kKc;
-  t.lane = threadIdx.x & 63;
-  t.wave = threadIdx.x >> 6;
-  const int h = t.lane >> 5, l32 = t.lane & 31;
-  const int wm0 = (t.wave / WN) * QM * 32, wn0 = (t.wave % WN) * QN * 32;
-
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(ISPA_LDS const void*)smem;
-  uint32_t oa[QM], ob[QN];
+  __syncthreads();
+  for (int s = 0; s < steps; ++s) {
+    const char* la = smem[s & 1];
+    const char* lb = la + kSide;
+    if (s == steps - 1) {  // the minuend's loads pass under the last stage's products
 #pragma unroll
-  for (int i = 0; i < QM; ++i) oa[i] = lds0 + h * TM * 4 + (((wm0 + 32 * i + l32) ^ (32 * h)) << 2);
+      for (int i = 0; i < Q; ++i)
 #pragma unroll
-  for (int j = 0; j < QN; ++j) ob[j] = lds0 + kKc * TM * 4 + h * TN * 4 + (((wn0 + 32 * j + l32) ^ (32 * h)) << 2);
-
-  f32x16 acc[QM][QN];
+        for (int j = 0; j < Q; ++j)
 #pragma unroll
-  for (int i = 0; i < QM; ++i)
+          for (int r = 0; r < 16; ++r)
+            cin[i][j][r] = __builtin_bit_cast(float, (u32)__builtin_amdgcn_raw_buffer_load_b32(
+                rc, coff + 128 * j, (32 * i + 8 * (r >> 2) + (r & 3)) * ldc4, 0));
+    }
 #pragma unroll
-    for (int j = 0; j < QN; ++j) acc[i][j] = f32x16{};
-
-  for (int s = 0; s < 3 && s < t.steps; ++s) ring_load<TM, TN>(t, smem, s);
-  if (t.steps >= 3) {
-    vm_wait<2 * kLoads>();
-  } else if (t.steps == 2) {
-    vm_wait<kLoads>();
-  } else {
-    vm_wait<0>();
+    for (int kk = 0; kk < kKs / 16; ++kk) {
+      bf16x8 a[Q][3], b[Q][3];
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          a[i][q] = *(const bf16x8*)(la + q * (kSide / 3) + SideA::slot(wm0 + 32 * i + l32, 2 * kk + h));
+          b[i][q] = *(const bf16x8*)(lb + q * (kSide / 3) + SideB::slot(wn0 + 32 * i + l32, 2 * kk + h));
+        }
+      }
+      // the smallest products first
+#pragma unroll
+      for (int pr = 0; pr < 6; ++pr) {
+        constexpr int pa[6] = {2, 1, 0, 1, 0, 0}, pb[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+#pragma unroll
+          for (int j = 0; j < Q; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][pa[pr]], b[j][pb[pr]], acc[i][j], 0, 0, 0);
+      }
+    }
+    // the other buffer was read in stage s - 1, before the last barrier
+    if (s + 1 < steps) {
+      if ((s + 2) * kKs > K) sa.mask((s + 1) * kKs, K);
+      sa.put(smem[(s + 1) & 1]);
+      sb.put(smem[(s + 1) & 1] + kSide);
+      if (s + 2 < steps) {
+        sa.load(s + 2);
+        sb.load(s + 2);
+      }
+      __syncthreads();
+    }
   }
-  __builtin_amdgcn_s_barrier();  // stage 0 has landed (vmcnt above)
-  for (int s = 0; s < t.steps; s += kRing) {
-    ring_stage<0, TM, TN, QM, QN>(t, smem, oa, ob, acc, s);
-    if (s + 1 < t.steps) ring_stage<1, TM, TN, QM, QN>(t, smem, oa, ob, acc, s + 1);
-    if (s + 2 < t.steps) ring_stage<2, TM, TN, QM, QN>(t, smem, oa, ob, acc, s + 2);
-    if (s + 3 < t.steps) ring_stage<3, TM, TN, QM, QN>(t, smem, oa, ob, acc, s + 3);
-  }
 
-  const int lane = t.lane;
 #pragma unroll
-  for (int i = 0; i < QM; ++i)
+  for (int i = 0; i < Q; ++i)
 #pragma unroll
-    for (int j = 0; j < QN; ++j) {
-      const int col = t.n0 + wn0 + 32 * j + l32;
+    for (int j = 0; j < Q; ++j) {
+      const int col = n0 + wn0 + 32 * j + l32;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int row = t.m0 + wm0 + 32 * i + acc_row(r, lane);
-        if (row < t.M && col < t.N) {
-          const int64_t o = (int64_t)row * ldc + col;
-          C[o] = sub ? Cin[o] - acc[i][j][r] : acc[i][j][r];
+        const int row = m0 + wm0 + 32 * i + acc_row(r, lane);
+        if (row < M && col < N) {
+          const int64_t o = (int64_t)row * jb.ldc + col;
+          C[o] = jb.Cin != nullptr ? cin[i][j][r] - acc[i][j][r] : acc[i][j][r];
         }
       }
     }
@@ -1169,15 +1190,27 @@ size_t solve_dinv_bytes(int d) {
 
 namespace {
 
-// Launches C (-)= A B over 64 x 64 output tiles, for `layers` layers.
-hipError_t launch_gemm(const GemmArgs& g, int layers, hipStream_t stream) {
-  int tiles = 0;
-  for (int j = 0; j < g.n_jobs; ++j) tiles += ((g.job[j].M + 63) / 64) * ((g.N + 63) / 64);
-  // 64 x 64 tiles at every size: 32 KB of LDS, so several workgroups share a CU
-  // and hide each other's load latency, and the last round is finely grained
-  // (measured against 128 x 128 and 128 x 64 tiles: the 5120-row solve takes
-  // 5.1 ms with 64 x 64 tiles throughout, 6.2 ms with 128 x 128)
-  hipLaunchKernelGGL((gemm_ring_kernel<2, 2, 1, 1>), dim3(tiles, 1, layers), dim3(kThreads), 0, stream, g);
+// Launches a split GEMM of up to two jobs for every layer: 128 x 128 tiles when
+// there is at least one for each compute unit, else 64 x 64. 128 x 128 tiles
+// halve the cutting and the operand reads per product (30 layers of 1536: the
+// whole batch 3.32 ms against 3.61 with 64 x 64 throughout; one layer of 5120
+// 4.15 against 4.41 ms) but leave the chip idle with fewer (one layer of 1536:
+// 0.79 ms against 0.64).
+constexpr int kSplitBigTiles = 256;
+template <bool A_KM>
+hipError_t launch_split(const SplitArgs& g, hipStream_t stream) {
+  auto tiles = [&](int T) {
+    int64_t n = 0;
+    for (int j = 0; j < g.n_jobs; ++j) n += (int64_t)((g.job[j].M + T - 1) / T) * ((g.N + T - 1) / T);
+    return n * g.layers;
+  };
+  const bool big = tiles(128) >= kSplitBigTiles;
+  const int grid = (int)((tiles(big ? 128 : 64) + 7) / 8 * 8);
+  if (big) {
+    hipLaunchKernelGGL((gemm_split_kernel<2, A_KM>), dim3(grid), dim3(kThreads), 0, stream, g);
+  } else {
+    hipLaunchKernelGGL((gemm_split_kernel<1, A_KM>), dim3(grid), dim3(kThreads), 0, stream, g);
+  }
   return hipGetLastError();
 }
 
@@ -1419,7 +1452,7 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
       }
     }
   }
-  // X_I, P_I = X_I^T X_I, Lh below the 256-block diagonal, its mirror above
+  // X_I, P_I = X_I^T X_I, Lh below the 256-block diagonal
   hipLaunchKernelGGL(inv256_kernel, dim3(nb, 4, nl), dim3(kThreads), 0, stream, L, w.dinv, xinv, d, ws);
   {
     GemmArgs g = {};
@@ -1452,7 +1485,6 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
     g.batch_dm = -kBb;
     hipLaunchKernelGGL((gemm_kernel<1, 4, 1, 2, true>), dim3((d - kBb + 31) / 32, nb - 1, nl), dim3(kThreads), 0,
                        stream, g);
-    hipLaunchKernelGGL(mirror_kernel, dim3(nblk * nblk, nl), dim3(kThreads), 0, stream, L, d, ws);
   }
   // The sweeps treat each column of the right-hand side on its own, so from
   // d = 4096 on the columns go in two halves, each on a stream of its own (the
@@ -1463,43 +1495,32 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
   // 0.97, 1536 0.66 -> 0.69 ms (halves too small to fill the chip).
   auto yblk = [&](auto* base, int I) { return base + (int64_t)I * kBb * d_out; };
   auto kblk = [&](int I) { return min(kBb, d - I * kBb); };
-  auto lup = [&](int I, int r) { return L + (int64_t)I * kBb * d + (int64_t)r * kBb; };  // rows of I, columns of r
+  auto low = [&](int r, int I) { return L + (int64_t)r * kBb * d + (int64_t)I * kBb; };  // rows of block r, columns of I
   auto sweeps = [&](int col0, int ncols, hipStream_t st) -> hipError_t {
     // forward sweep: Y_r -= Lh_rI Y_I (r > I) and dW_I = P_I Y_I. After the first
     // block the blocks go in pairs (I, I+1): one launch finishes Y_{I+1} and forms
     // dW_I, the next updates every later block with both (depth 512, so the
     // read-modify-write of the right-hand side below is shared by two blocks)
-    // and forms dW_{I+1}. The A operand is the mirrored Lh above the diagonal,
-    // whose rows I*256 .. of blocks I and I+1 are consecutive. Row pointers of
+    // and forms dW_{I+1}. The A operand is the rows of Lh below, whose columns of
+    // blocks I and I+1 are consecutive. Row pointers of
     // the right-hand side, Y and dW are taken at column 0 and moved to col0 here.
     auto fwd_launch = [&](const float* A, float* Ydst, const float* Ysrc, int M, const float* Bsum, int Ksum,
                           int P, const float* Bp, int Kp) -> hipError_t {
-      GemmArgs g = {};
+      SplitArgs g = {};
       int j = 0;
-      if (M > 0) {
-        g.job[j] = GemmJob{A, Ydst + col0, M, d, d_out, 1, Ysrc + col0};
-        g.job[j].la = g.job[j].lc = ws;
-        g.job[j].B = Bsum + col0;
-        g.job[j].K = Ksum;
-        ++j;
-      }
-      g.job[j] = GemmJob{pinv + (int64_t)P * kBb * kBb, delta_w + (int64_t)P * kBb * d_out + col0, Kp, kBb, d_out, 0};
-      g.job[j].la = ws;
-      g.job[j].lc = dws;
-      g.job[j].B = Bp + col0;
-      g.job[j].K = Kp;
-      ++j;
+      if (M > 0) g.job[j++] = SplitJob{A, Ydst + col0, Ysrc + col0, Bsum + col0, M, Ksum, d, d_out, ws, ws};
+      g.job[j++] = SplitJob{pinv + (int64_t)P * kBb * kBb, delta_w + (int64_t)P * kBb * d_out + col0, nullptr,
+                            Bp + col0, Kp, Kp, kBb, d_out, ws, dws};
       g.n_jobs = j;
-      g.lb = ws;
-      g.B = Bp + col0;
       g.N = ncols;
-      g.K = Kp;
+      g.layers = nl;
       g.ldb = d_out;
-      return launch_gemm(g, nl, st);
+      g.lb = ws;
+      return launch_split<false>(g, st);
     };
     hipError_t e;
     // the first step reads the right-hand side C itself (Y = C before any update)
-    e = fwd_launch(lup(0, 1), yblk(Y, 1), yblk(C, 1), d - kBb, C, kblk(0), 0, C, kblk(0));
+    e = fwd_launch(low(1, 0), yblk(Y, 1), yblk(C, 1), d - kBb, C, kblk(0), 0, C, kblk(0));
     if (e != hipSuccess) return e;
     for (int I = 1; I < nb; I += 2) {
       if (I + 1 == nb) {
@@ -1507,11 +1528,11 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
         if (e != hipSuccess) return e;
         break;
       }
-      e = fwd_launch(lup(I, I + 1), yblk(Y, I + 1), yblk(Y, I + 1), kblk(I + 1), yblk(Y, I), kBb, I, yblk(Y, I),
+      e = fwd_launch(low(I + 1, I), yblk(Y, I + 1), yblk(Y, I + 1), kblk(I + 1), yblk(Y, I), kBb, I, yblk(Y, I),
                      kBb);
       if (e != hipSuccess) return e;
       const int below = d - (I + 2) * kBb;
-      e = fwd_launch(below > 0 ? lup(I, I + 2) : nullptr, below > 0 ? yblk(Y, I + 2) : Y,
+      e = fwd_launch(below > 0 ? low(I + 2, I) : nullptr, below > 0 ? yblk(Y, I + 2) : Y,
                      below > 0 ? yblk(Y, I + 2) : Y, max(below, 0), yblk(Y, I), kBb + kblk(I + 1), I + 1,
                      yblk(Y, I + 1), kblk(I + 1));
       if (e != hipSuccess) return e;
@@ -1520,17 +1541,15 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
     // pairs (J, J-1): one launch finishes dW_{J-1}, the next updates every earlier
     // block with both (rows (J-1)*256 .. of L, depth 512); rows from row0 on
     auto bwd_launch = [&](int J, int M, int K, int row0) -> hipError_t {
-      GemmArgs g = {};
-      g.job[0] = GemmJob{L + (int64_t)J * kBb * d + row0, delta_w + (int64_t)row0 * d_out + col0, M, d, d_out, 1};
-      g.job[0].la = ws;
-      g.job[0].lc = dws;
-      g.lb = dws;
+      SplitArgs g = {};
+      float* dst = delta_w + (int64_t)row0 * d_out + col0;
+      g.job[0] = SplitJob{L + (int64_t)J * kBb * d + row0, dst, dst, yblk(delta_w, J) + col0, M, K, d, d_out, ws, dws};
       g.n_jobs = 1;
-      g.B = yblk(delta_w, J) + col0;
       g.N = ncols;
-      g.K = K;
+      g.layers = nl;
       g.ldb = d_out;
-      return launch_gemm(g, nl, st);
+      g.lb = dws;
+      return launch_split<true>(g, st);
     };
     for (int J = nb - 1; J >= 1; J -= 2) {
       e = bwd_launch(J, kBb, kblk(J), (J - 1) * kBb);

@@ -287,6 +287,26 @@ def test_batch_solve_wan13b_size():
         assert float(eps_b[i].item()) == float(eps_1.item())
 
 
+@pytest.mark.parametrize("d,d_out,layers", [(264, 72, 96), (520, 136, 40), (776, 392, 16)])
+def test_batch_solve_large_tiles_ragged(d, d_out, layers):
+    # enough layers that the sweeps take their 128 x 128 tiles, at widths that
+    # end inside a tile, a 16-k stage and a 256-block: bit for bit the
+    # single-layer solve (64 x 64 tiles), and the oracle's dW
+    lam, n = 0.5, 2 * d
+    sb = ispa.StatsBatch(layers, d, d_out, max_rows=n, device=DEV)
+    _fill_batch(sb, 43, n)
+    dw_b, eps_b, status_b = sb.solve(lam)
+    torch.cuda.synchronize()
+    assert status_b.tolist() == [0] * layers
+    for i in (0, layers // 2, layers - 1):
+        dw_1, eps_1, _ = sb.layers[i].solve_async(lam)
+        torch.cuda.synchronize()
+        assert torch.equal(dw_b[i].view(torch.int32), dw_1.view(torch.int32))
+        G, C, _, _ = sb.layers[i].views()
+        g = np.tril(f64(G))
+        assert rel_fro(f64(dw_1), oracle.solve_modulation(g + np.tril(g, -1).T, f64(C), lam)) <= 1e-5
+
+
 def test_batch_matches_single_with_look_ahead():
     # d = 3072 (48 panels): the single-layer factorisation takes its look-ahead
     # form (panel groups applied by extra workgroups of later panel launches),
