@@ -11,23 +11,30 @@
 // Cholesky, one launch per panel (right-looking, the next panel fused in):
 //   launch k (k = -1 .. nb-2) owns the trailing lower block triangle from
 //   block k+1 on. Workgroups on the next panel column (r, k+1) apply the rank-64
-//   update of panel k to the diagonal block A_{k+1,k+1} (each its own copy in
-//   LDS), factor it, invert the factor, and turn their block into
-//   L_{r,k+1} = (A_{r,k+1} - L_{r,k} L_{k+1,k}^T) L_{k+1,k+1}^-T. All other
-//   workgroups apply A_rt -= L_rk L_tk^T. The diagonal blocks themselves are
-//   never overwritten (other workgroups of the same launch read them); their
-//   inverses go to Dinv.
-// Factor + inverse of one 64 x 64 block (one wave, the others wait): 32 x 32
-//   sub-blocks, each reduced in registers with the pivot row broadcast by
-//   readlane, the inverse formed in the same instructions by the other half of
-//   the wave; the off-diagonal pieces are 32 x 32 x 32 MFMA products.
+//   update of panel k to their block and to the diagonal block A_{k+1,k+1} (each
+//   its own copy in LDS), and run the rows of both through one elimination: the
+//   diagonal block's rows become its factor and the block's rows
+//   L_{r,k+1} = (A_{r,k+1} - L_{r,k} L_{k+1,k}^T) L_{k+1,k+1}^-T in the same
+//   steps. All other workgroups apply A_rt -= L_rk L_tk^T. The diagonal blocks
+//   themselves are never overwritten (other workgroups of the same launch read
+//   them); their inverses (the identity run through the elimination by the
+//   diagonal block's own workgroup) go to Dinv.
+// The elimination is bound by its latency: 64 pivots, one after the other. It
+//   runs in registers, a matrix row per lane, 16 columns at a time, the pivot row
+//   reaching all lanes as a DPP broadcast inside the multiply-add (4 + 2 (15 - j)
+//   instructions at step j); between the 16-column pieces the four waves apply
+//   them as 16x16x4 MFMAs. A panel launch takes 10.5 us at the 1536-row solve
+//   (15.5 with a factor and inverse by readlane, a product with the inverse and
+//   loads behind a branch each): 1.5K cycles to issue the loads, 5.7K for their
+//   latency, the cut and the products, four times 1.8K of elimination and 1.6K
+//   of LDS traffic, updates and barriers.
 // Triangular solves in block LDL^T form over 256-blocks (details below): the
 //   inverses X_I of the 256 x 256 diagonal blocks of L and P_I = X_I^T X_I,
 //   Lh = L diag(X_I) below the 256-block diagonal, then one right-looking
 //   rank-256 GEMM launch per block for the forward and for the backward sweep,
 //   with no diagonal work in them.
-// The sweeps' products run on the bf16 matrix cores with every fp32 operand cut
-// into three bf16 parts (below); the others are fp32 MFMA.
+// The panel updates and the sweeps run on the bf16 matrix cores with every fp32
+// operand cut into three bf16 parts (below); the other products are fp32 MFMA.
 // Several layers at once (the end of warmup solves every layer): every kernel
 // takes its layer from the last grid dimension and offsets its workspace
 // pointers by the layers' workspace stride (dW by its own stride), so one
@@ -79,32 +86,6 @@ __device__ __forceinline__ void mma(f32x16& acc, const float (*A)[kLd], int a0, 
 // accumulator element r of lane l sits at (row, col) of the 32 x 32 quadrant
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 
-// 16 x 16 pieces (v_mfma_f32_16x16x4f32): lane l supplies A[l % 16][k + l / 16]
-// and B[k + l / 16][l % 16]; accumulator element r of lane l sits at row
-// 4 (l / 16) + r, column l % 16.
-// acc = op(A)[a0 .., ak ..] op(B)[bk .., b0 ..] over K, same conventions as mma.
-template <bool TA, bool TB, int K>
-__device__ __forceinline__ f32x4 mma16(const float (*A)[kLd], int a0, int ak, const float (*B)[kLd], int b0, int bk,
-                                       int lane) {
-  const int i = lane & 15, kq = lane >> 4;
-  f32x4 acc = {};
-#pragma unroll
-  for (int k = 0; k < K; k += 4) {
-    const float a = TA ? A[ak + k + kq][a0 + i] : A[a0 + i][ak + k + kq];
-    const float b = TB ? B[b0 + i][bk + k + kq] : B[bk + k + kq][b0 + i];
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
-  }
-  return acc;
-}
-// D[r0 ..][c0 ..] (16 x 16) = sign * acc, or += sign * acc
-__device__ __forceinline__ void put16(Tile& D, int r0, int c0, const f32x4& acc, float sign, bool add, int lane) {
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    float& d = D[r0 + 4 * (lane >> 4) + r][c0 + (lane & 15)];
-    d = add ? d + sign * acc[r] : sign * acc[r];
-  }
-}
-
 // A 64 x 64 block of a row-major matrix (ld) in flight: four 16-byte pieces per
 // thread. Rows >= rows_ok or cols >= cols_ok read as zero (ragged last block).
 // Row starts are 16-byte aligned and cols_ok is a multiple of 4 (dimensions are
@@ -148,153 +129,236 @@ __device__ __forceinline__ void store_tile(const Tile& t, float* dst, int64_t ld
   }
 }
 
-__device__ __forceinline__ float readlane_f(float v, int l) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+typedef unsigned int u32;
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// x[0..7] cut into three bf16 chunks of 8
+__device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&p)[3]) {
+  // (-1, 0) and (0, -1) as packed bf16, kept out of the compiler's sight: as an
+  // inline constant of a packed operand -1.0 is taken for the wrong half
+  u32 lo = 0x0000bf80u, hi = 0xbf800000u;
+  asm("" : "+s"(lo), "+s"(hi));
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float a = x[2 * j], b = x[2 * j + 1];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const bf16x2 w = __builtin_convertvector((f32x2{a, b}), bf16x2);
+      p[q][j] = __builtin_bit_cast(u32, w);
+      if (q < 2) {  // what the part left: one multiply-add with the pair, exact
+        a = __builtin_amdgcn_fdot2_f32_bf16(w, __builtin_bit_cast(bf16x2, lo), a, false);
+        b = __builtin_amdgcn_fdot2_f32_bf16(w, __builtin_bit_cast(bf16x2, hi), b, false);
+      }
+    }
+  }
 }
 
-// Orders the LDS accesses of one wave around this point. A wave's LDS
-// operations are performed in issue order, so only the compiler has to be kept
-// from moving them.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+
+// Wave-uniform wave index (a scalar, so that a wave's branch is a scalar branch).
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+
+// Rows 0 .. rows - 1 of a row-major matrix as a buffer: loads past them read zero
+// and stores past them are dropped, without a branch around each. Offsets in
+// bytes, per lane (kNoCol where its column is outside) plus a scalar one; the
+// hardware tests their sum, also where the scalar one alone is past the end.
+constexpr int kNoCol = (int)0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const float* base, int64_t ld, int rows) {
+  int64_t nrec = rows > 0 ? rows * ld * 4 : 0;
+  if (nrec > 0x7fffffff) nrec = 0x7fffffff;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)nrec, 0x00020000);
+}
+__device__ __forceinline__ float ld1(__amdgpu_buffer_rsrc_t rs, int off, int soff) {
+  return __builtin_bit_cast(float, (u32)__builtin_amdgcn_raw_buffer_load_b32(rs, off, soff, 0));
+}
+__device__ __forceinline__ f32x4 ld4(__amdgpu_buffer_rsrc_t rs, int off) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+}
+__device__ __forceinline__ void st1(__amdgpu_buffer_rsrc_t rs, int off, int soff, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(u32, v), rs, off, soff, 0);
 }
 
-// One wave: factor the N x N SPD block S[o..o+N-1][o..o+N-1] (N = 16 or 32,
-// lower part valid) into L, in place with zeros above the diagonal, and write
-// L^-1 (lower triangular) to M[o..][o..]. No LDS traffic inside the elimination:
-//   lanes 0..N-1    x = row i of the symmetric matrix being reduced,
-//   lanes N..2N-1   x = column i - N of the inverse being formed by forward
-//                   substitution, starting from the unit vector
-// (for N = 16 lanes 32..63 repeat lanes 0..31 and store nothing).
-// At step j the pivot p_j = (row j)[j] and s_c = (row j)[c] = (column j)[c]
-// (symmetry) come from lane j by readlane, and both kinds of lane apply the
-// same update x[c] -= (x[j] / p_j) s_c for c > j: the Schur complement for a
-// row, the substitution step m_c -= L_cj m_j / L_jj for an inverse column.
-// Afterwards L[i][j] = x[j] / sqrt(p_j) (j < i), L[i][i] = sqrt(p_i) and
-// L^-1[r][col] = x[r] / sqrt(p_r). Hardware square root and reciprocal (about
-// 1 ulp). Sets *bad on a non-positive pivot (then replaced by 1).
+// A 64 x 64 fp32 tile with 16-byte aligned rows: 16 rows of a column chunk fall
+// into different banks both as 16-byte pieces (a row each) and as the 4-byte
+// operands of a 16 x 16 product.
+constexpr int kLd4 = 68;
+typedef float RowTile[kNb][kLd4];
+
+// 16 steps of elimination on the register rows of one wave. y: the 16 x 16
+// pivot block, row l % 16 (symmetric, all 16 columns) in lane l, four copies;
+// x: 16 columns of one matrix row per lane. At step j the pivot p = y[j] of
+// lane j and its row s_c = y[c] reach every lane as DPP row broadcasts inside
+// the multiply-adds, and
+//   x[c] -= (x[j] / p) s_c,   y[c] -= (y[j] / p) s_c   (c > j).
+// Lane j keeps p; at the end column j of x is divided by sqrt(p_j) (hardware square
+// root and reciprocal, about 1 ulp each). Afterwards x holds the row times L^-T of the pivot block, a row of the
+// factor L. Returns the lane's pivot: not positive where the block is not SPD.
+// One asm block on fixed registers, so that the waits it needs are its own: a
+// DPP operand is read at least two instructions after it is written, a
+// reciprocal at least one after it is issued.
+__device__ __forceinline__ float elim16(f32x16& y, f32x16& x) {
+  float r, ny, nx, piv;
+  unsigned long long lane_j = 0x0001000100010001ull;  // lane j of each row of 16
+  asm volatile(
+      "s_nop 1\n"
+      "v_mov_b32 %[p], 0\n"
+      ".set ej, 0\n"
+      ".rept 16\n"
+      ".if ej == 15\n"
+      "s_nop 1\n"
+      ".endif\n"
+      "v_rcp_f32_dpp %[r], v[32+ej] row_newbcast:ej row_mask:0xf bank_mask:0xf\n"
+      "v_cndmask_b32 %[p], %[p], v[32+ej], %[m]\n"
+      "s_lshl_b64 %[m], %[m], 1\n"
+      "v_mul_f32 %[nx], v[48+ej], -%[r]\n"
+      "v_mul_f32 %[ny], v[32+ej], -%[r]\n"
+      ".set ec, ej + 1\n"
+      ".rept 15 - ej\n"
+      "v_fmac_f32_dpp v[48+ec], v[32+ec], %[nx] row_newbcast:ej row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f32_dpp v[32+ec], v[32+ec], %[ny] row_newbcast:ej row_mask:0xf bank_mask:0xf\n"
+      ".set ec, ec + 1\n"
+      ".endr\n"
+      ".set ej, ej + 1\n"
+      ".endr\n"
+      "v_sqrt_f32 %[r], %[p]\n"
+      "s_nop 1\n"
+      "v_rcp_f32 %[r], %[r]\n"
+      "s_nop 1\n"
+      ".set ej, 0\n"
+      ".rept 16\n"
+      "v_mul_f32_dpp v[48+ej], %[r], v[48+ej] row_newbcast:ej row_mask:0xf bank_mask:0xf\n"
+      ".set ej, ej + 1\n"
+      ".endr\n"
+      : "+{v[32:47]}"(y), "+{v[48:63]}"(x), [r] "=&v"(r), [ny] "=&v"(ny), [nx] "=&v"(nx), [p] "=&v"(piv),
+        [m] "+s"(lane_j)
+      :
+      : "scc");
+  return piv;
+}
+
+// D -= X_T X_S^T for up to two 16 x 16 pieces: D = T[16 i ..][16 c ..], X_T and X_S
+// the rows 16 i of T and 16 c of S at columns 16 b. All reads are issued first.
+struct Piece {
+  RowTile* T;
+  int i, c;
+};
 template <int N>
-__device__ __forceinline__ void factor_reg(Tile& S, Tile& M, int o, int lane, int* bad) {
-  const int i = lane % N;
-  const bool lo = (lane / N) % 2 == 0;
-  float x[N];
+__device__ __forceinline__ void update16(const Piece (&p)[N], const RowTile& S, int b, int lane) {
+  const int l16 = lane & 15, g = lane >> 4;
+  float x[N][4], y[N][4], d[N][4];
 #pragma unroll
-  for (int c = 0; c < N; ++c) {
-    float v = S[o + max(i, c)][o + min(i, c)];
-    asm volatile("" : "+v"(v));  // every lane loads: no branch around the read
-    x[c] = lo ? v : (c == i ? 1.f : 0.f);
-  }
-  float lj[N];
-  int neg = 0;
+  for (int u = 0; u < N; ++u)
 #pragma unroll
-  for (int j = 0; j < N; ++j) {
-    float piv = readlane_f(x[j], j);
-    neg |= !(piv > 0.f);
-    piv = piv > 0.f ? piv : 1.f;
-    lj[j] = piv;
-    // the pivot row first (independent readlanes), then the updates
-    float sr[N];
-#pragma unroll
-    for (int c = j + 1; c < N; ++c) sr[c] = readlane_f(x[c], j);
-    const float coef = x[j] * __builtin_amdgcn_rcpf(piv);
-#pragma unroll
-    for (int c = j + 1; c < N; ++c) x[c] = fmaf(-coef, sr[c], x[c]);
-  }
-  if (neg && lane == 0) *bad = 1;
-  // one store per element: row i of L for the row lanes, column i of L^-1 for the rest
-  float* dst = lo ? &S[o + i][o] : &M[o][o + i];
-  const int step = lo ? 1 : kLd;
-  if (lane < 2 * N) {
-#pragma unroll
-    for (int c = 0; c < N; ++c) {
-      const float l = __builtin_amdgcn_sqrtf(lj[c]);
-      const float v = x[c] * __builtin_amdgcn_rcpf(l);
-      dst[c * step] = lo ? (c < i ? v : (c == i ? l : 0.f)) : (c >= i ? v : 0.f);
+    for (int k = 0; k < 4; ++k) {
+      x[u][k] = (*p[u].T)[16 * p[u].i + l16][16 * b + 4 * k + g];
+      y[u][k] = S[16 * p[u].c + l16][16 * b + 4 * k + g];
+      d[u][k] = (*p[u].T)[16 * p[u].i + 4 * g + k][16 * p[u].c + l16];
     }
-  }
-  wave_sync();
+  f32x4 acc[N] = {};
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+#pragma unroll
+    for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][k], y[u][k], acc[u], 0, 0, 0);
+#pragma unroll
+  for (int u = 0; u < N; ++u)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) (*p[u].T)[16 * p[u].i + 4 * g + k][16 * p[u].c + l16] = d[u][k] - acc[u][k];
 }
 
-// One wave: the 32 x 32 factor and inverse at offset o from two 16 x 16 register
-// factors: L00 and M00; L10 = S10 M00^T; S11 -= L10 L10^T with T = L10 M00
-// beside it (T in the upper-right 16 x 16 of this block of M, zero again at the
-// end); L11 and M11; M10 = -M11 T. The 16-wide eliminations issue a third of the
-// readlanes and FMAs of one 32-wide elimination, and the products are four
-// 16x16x4 MFMAs each.
-__device__ __forceinline__ void factor32(Tile& S, Tile& M, int o, int lane, int* bad) {
-  factor_reg<16>(S, M, o, lane, bad);
-  {
-    const f32x4 l10 = mma16<false, true, 16>(S, o + 16, o, M, o, o, lane);
-    put16(S, o + 16, o, l10, 1.f, false, lane);  // in place: its reads are issued before
-  }
-  wave_sync();
-  {
-    const f32x4 u = mma16<false, true, 16>(S, o + 16, o, S, o + 16, o, lane);
-    const f32x4 t = mma16<false, false, 16>(S, o + 16, o, M, o, o, lane);
-    put16(S, o + 16, o + 16, u, -1.f, true, lane);
-    put16(M, o, o + 16, t, 1.f, false, lane);
-  }
-  wave_sync();
-  factor_reg<16>(S, M, o + 16, lane, bad);
-  {
-    const f32x4 m10 = mma16<false, false, 16>(M, o + 16, o + 16, M, o + 16, o, lane);
-    put16(M, o + 16, o, m10, -1.f, false, lane);
-    put16(M, o, o + 16, f32x4{}, 1.f, false, lane);
-  }
-  wave_sync();
-}
-
-// Factor the 64 x 64 SPD block in S (lower part valid, zero above) into L (in
-// place) and write L^-1 to M; T is scratch. All threads call; wave 0 factors.
-// With P given, waves 1..3 meanwhile apply P -= Q R^T (the panel block's own
-// rank-64 update, independent of the factor), quadrant q on wave 1 + q % 3.
-__device__ void factor64(Tile& S, Tile& M, Tile& T, int nb, int* bad, Tile* P, const Tile* Q, const Tile* R) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // a ragged last block: identity beyond nb keeps the factorisation defined
-  if (nb < kNb) {
-    for (int e = threadIdx.x; e < kNb * kNb; e += kThreads) {
-      const int r = e >> 6, c = e & 63;
-      if (r >= nb || c >= nb) S[r][c] = r == c ? 1.f : 0.f;
-    }
-  }
-  // the quadrant of L^-1 above the diagonal; factor32 writes the other three
-  for (int e = threadIdx.x; e < 32 * 32; e += kThreads) M[e >> 5][32 + (e & 31)] = 0.f;
-  __syncthreads();
-  // the 32 x 32 products below are split over the four waves, 16 x 16 each
-  const int qr = 16 * (wave >> 1), qc = 16 * (wave & 1);
-  if (wave == 0) {
-    factor32(S, M, 0, lane, bad);
-  } else if (P) {
-    for (int q = wave - 1; q < 4; q += 3) {
-      const int r0 = (q >> 1) * 32, c0 = (q & 1) * 32;
-      f32x16 acc = {};
-      mma<false, true>(acc, *Q, r0, 0, *R, c0, 0, kNb, lane);
+// Factor the 64 x 64 SPD block in S (lower part valid, its diagonal 16 x 16
+// pieces symmetric) into L in place, and turn the 64 rows in Q into Q L^-T (the
+// panel block's rows, or the identity, which becomes L^-T). All four waves
+// call, after a barrier that follows the writes of S and Q. 16 columns at a
+// time: waves 0 and 1 eliminate them in the rows of S and Q (each with its own
+// copy of the pivot block), all waves then apply them to the next 16 columns,
+// and waves 2 and 3 to the columns after those during the next elimination.
+// Sets *bad on a non-positive pivot.
+__device__ __forceinline__ void factor_rows(RowTile& S, RowTile& Q, int* bad) {
+  const int lane = threadIdx.x & 63, wave = wave_id();
+#pragma unroll 1
+  for (int b = 0; b < 4; ++b) {
+    RowTile& T = wave == 0 ? S : Q;
+    f32x16 y, x;
+    if (wave < 2) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) (*P)[r0 + acc_row(r, lane)][c0 + (lane & 31)] -= acc[r];
+      for (int c = 0; c < 4; ++c) {
+        const f32x4 v = *(const f32x4*)&S[16 * b + (lane & 15)][16 * b + 4 * c];
+        const f32x4 w = *(const f32x4*)&T[lane][16 * b + 4 * c];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          y[4 * c + j] = v[j];
+          x[4 * c + j] = w[j];
+        }
+      }
     }
-  }
-  __syncthreads();
-  // L10 = S10 . M00^T (in place: all reads before the stores)
-  {
-    const f32x4 acc = mma16<false, true, 32>(S, 32 + qr, 0, M, qc, 0, lane);
+    __syncthreads();  // wave 1 holds the pivot block: wave 0 may overwrite it
+    if (wave < 2) {
+      const float piv = elim16(y, x);
+      if (wave == 0 && !(piv > 0.f)) *bad = 1;
+      const int own = wave == 0 ? lane - 16 * b : kNb;  // row of S from the pivot block on
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        f32x4 v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = own < 4 * c + j ? 0.f : x[4 * c + j];
+        *(f32x4*)&T[lane][16 * b + 4 * c] = v;
+      }
+    } else if (b > 0) {
+      // the last 16 columns' updates past the next ones
+      for (int c = b + 1; c < 4; ++c) {
+        for (int i = c + wave - 2; i < 4; i += 2) update16<1>({{&S, i, c}}, S, b - 1, lane);
+        update16<2>({{&Q, wave - 2, c}, {&Q, wave, c}}, S, b - 1, lane);
+      }
+    }
     __syncthreads();
-    put16(S, 32 + qr, qc, acc, 1.f, false, lane);
+    if (b < 3) {
+      // 3 - b pieces of S and 4 of Q, the first of S (the next pivot block) on wave 3
+      const int c = b + 1;
+      if (wave < 2 - b) {
+        update16<2>({{&S, c + 1 + wave, c}, {&Q, wave, c}}, S, b, lane);
+      } else if (wave < 3) {
+        update16<1>({{&Q, wave, c}}, S, b, lane);
+      } else {
+        update16<2>({{&S, c, c}, {&Q, 3, c}}, S, b, lane);
+      }
+      __syncthreads();
+    }
   }
-  __syncthreads();
-  // S11 -= L10 . L10^T and T = L10 . M00 (for M10 = -M11 . L10 . M00)
-  {
-    const f32x4 u = mma16<false, true, 32>(S, 32 + qr, 0, S, 32 + qc, 0, lane);
-    const f32x4 t = mma16<false, false, 32>(S, 32 + qr, 0, M, qc, 0, lane);
-    put16(S, 32 + qr, 32 + qc, u, -1.f, true, lane);
-    put16(T, qr, qc, t, 1.f, false, lane);
+}
+
+// Panel products on the bf16 matrix cores (three-way cut operands): 64 rows x 32
+// k of an operand are a half tile of three LDS planes of 64-byte rows, chunk c of
+// row r at c ^ (r / 4 mod 4). Every place that applies a panel to a block sums
+// its 64 k in the same order and subtracts the product on its own, so all forms
+// of the factorisation give the same bits.
+constexpr int kHalfTile = 64 * 64 * 3;  // bytes
+struct Chunk {
+  float v[8];
+};
+// 8 k of one row, at byte off
+__device__ __forceinline__ void fetch8(Chunk& f, __amdgpu_buffer_rsrc_t rs, int off) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const f32x4 w = ld4(rs, off + 16 * q);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f.v[4 * q + j] = w[j];
   }
-  __syncthreads();
-  if (wave == 0) factor32(S, M, 32, lane, bad);
-  __syncthreads();
-  // M10 = -M11 . T
-  put16(M, 32 + qr, qc, mma16<false, false, 32>(M, 32 + qr, 32, T, qc, 0, lane), -1.f, false, lane);
-  __syncthreads();
+}
+__device__ __forceinline__ int half_slot(int r, int c) { return r * 64 + ((c ^ ((r >> 2) & 3)) << 4); }
+__device__ __forceinline__ void put8(char* half, const Chunk& f, int r, int c) {
+  u32x4 p[3];
+  split8(f.v, p);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) *(u32x4*)(half + q * 4096 + half_slot(r, c)) = p[q];
+}
+__device__ __forceinline__ void read3(bf16x8 (&o)[3], const char* half, int r, int c) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) o[q] = *(const bf16x8*)(half + q * 4096 + half_slot(r, c));
+}
+// acc += A B^T over 16 k: the six products, the smallest first
+__device__ __forceinline__ void mma6(f32x16& acc, const bf16x8 (&a)[3], const bf16x8 (&b)[3]) {
+  constexpr int pa[6] = {2, 1, 0, 1, 0, 0}, pb[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+  for (int p = 0; p < 6; ++p) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pa[p]], b[pb[p]], acc, 0, 0, 0);
 }
 
 // Quadrant product over a full 64-deep tile pair, one quadrant per wave:
@@ -352,75 +416,90 @@ __global__ void solve_init_kernel(const float* G, float* L, int n, float lambda,
 // with top-left block (R, T), R >= T: A_rt -= L_rp L_tp^T for p in order, block
 // (R + w / 2, T + w % 2) on wave w (blocks past the matrix, above the diagonal
 // or in a column >= t_end are skipped). The four waves share L_rp (rows of
-// blocks R, R + 1) and L_tp staged in LDS, one panel at a time, the next
-// panel's tiles loaded into registers during this one's MFMAs; each wave's C
-// block stays in registers from the first panel to the last. Each panel's
-// product is subtracted on its own, in panel order, so the result is bit for
-// bit that of one launch per panel.
+// blocks R, R + 1) and L_tp, cut and staged in LDS half a panel (32 k) at a time,
+// loaded into registers two halves ahead; each wave's C block stays in registers
+// from the first panel to the last, its loads under the first half's products.
+// Each panel's product is subtracted on its own, in panel order, so the result
+// is bit for bit that of one launch per panel. Half a panel takes about 3.7K
+// cycles of a lone workgroup, 1.5K of them MFMAs (30 layers of 1536: the five
+// deferred updates 461 us with fp32 MFMAs, 285 here).
 template <int NP>
-__device__ __forceinline__ void trailing_2x2(float* L, int n, int nblk, int p0, int R, int T, int t_end, Tile* tiles) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__device__ __forceinline__ void trailing_2x2(float* L, int n, int nblk, int p0, int R, int T, int t_end, char* lds) {
+  const int lane = threadIdx.x & 63, wave = wave_id();
   const int l32 = lane & 31, h = lane >> 5;
-  float (*Ub)[kLd] = tiles[0];  // [128][kLd]: rows of blocks R, R + 1 (two consecutive tiles)
-  float (*Vb)[kLd] = tiles[2];  // [128][kLd]: rows of blocks T, T + 1
   const int br = R + (wave >> 1), bc = T + (wave & 1);
   const bool mine = br < nblk && bc <= br && bc < t_end;
-  const int rows_r0 = min(kNb, n - R * kNb), rows_r1 = min(kNb, n - (R + 1) * kNb);
-  const int rows_t0 = min(kNb, n - T * kNb), rows_t1 = min(kNb, n - (T + 1) * kNb);
-  Frag f0, f1, f2, f3;
-  fetch(f0, L + (int64_t)R * kNb * n + p0 * kNb, n, rows_r0, kNb);
-  fetch(f1, L + (int64_t)(R + 1) * kNb * n + p0 * kNb, n, rows_r1, kNb);
-  fetch(f2, L + (int64_t)T * kNb * n + p0 * kNb, n, rows_t0, kNb);
-  fetch(f3, L + (int64_t)(T + 1) * kNb * n + p0 * kNb, n, rows_t1, kNb);
+  // half tile q: rows of block R, R + 1, T, T + 1; this thread's row and chunk
+  const int row = threadIdx.x >> 2, chunk = threadIdx.x & 3;
+  const int n4 = n * 4;
+  const __amdgpu_buffer_rsrc_t rr = rows_rsrc(L + (int64_t)R * kNb * n, n, n - R * kNb);
+  const __amdgpu_buffer_rsrc_t rt = rows_rsrc(L + (int64_t)T * kNb * n, n, n - T * kNb);
+  Chunk f[2][4];  // the next two stages (the two halves of a panel)
+  auto load = [&](Chunk (&f)[4], int s) {
+    const int off = row * n4 + ((p0 + s / 2) * kNb + (s & 1) * 32 + chunk * 8) * 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) fetch8(f[q], q < 2 ? rr : rt, off + (q & 1) * kNb * n4);
+  };
+  load(f[0], 0);
+  load(f[1], 1);
+  const __amdgpu_buffer_rsrc_t rb = rows_rsrc(L + (int64_t)br * kNb * n, n, n - br * kNb);
+  int cof[2];  // column of block j of the accumulators, first row
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int col = bc * kNb + 32 * j + l32;
+    cof[j] = col < n ? 4 * h * n4 + col * 4 : kNoCol;
+  }
   float c[2][2][16];
-  if (mine) {
+  const char* const la = lds + (wave >> 1) * kHalfTile;
+  const char* const lb = lds + (2 + (wave & 1)) * kHalfTile;
+  f32x16 acc[2][2];
+#pragma unroll 1
+  for (int p = 0; p < NP; ++p) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (p + half > 0) __syncthreads();  // every wave is done with the previous stage
+#pragma unroll
+      for (int q = 0; q < 4; ++q) put8(lds + q * kHalfTile, f[half][q], row, chunk);
+      if (p + 1 < NP) load(f[half], 2 * (p + 1) + half);
+      __syncthreads();
+      if (!mine) continue;
+      if (p + half == 0) {  // the blocks themselves: needed after the panel's products
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) c[i][j][r] = ld1(rb, cof[j], (32 * i + acc_row(r, 0)) * n4);
+      }
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        bf16x8 a[2][3], b[2][3];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          read3(a[i], la, 32 * i + l32, 2 * kk + h);
+          read3(b[i], lb, 32 * i + l32, 2 * kk + h);
+        }
+        constexpr int pa[6] = {2, 1, 0, 1, 0, 0}, pb[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+        for (int pr = 0; pr < 6; ++pr)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][pa[pr]], b[j][pb[pr]], acc[i][j], 0, 0, 0);
+      }
+    }
+    if (!mine) continue;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = br * kNb + 32 * i + acc_row(r, lane), col = bc * kNb + 32 * j + l32;
-          c[i][j][r] = row < n && col < n ? L[(int64_t)row * n + col] : 0.f;
-        }
-  }
-  const int qr = (wave >> 1) * kNb, qc = (wave & 1) * kNb;
-#pragma unroll
-  for (int pi = 0; pi < NP; ++pi) {
-    const int p = p0 + pi;
-    if (pi > 0) __syncthreads();  // every wave is done with the previous panel's tiles
-    put(tiles[0], f0);
-    put(tiles[1], f1);
-    put(tiles[2], f2);
-    put(tiles[3], f3);
-    __syncthreads();
-    if (pi + 1 < NP) {
-      fetch(f0, L + (int64_t)R * kNb * n + (p + 1) * kNb, n, rows_r0, kNb);
-      fetch(f1, L + (int64_t)(R + 1) * kNb * n + (p + 1) * kNb, n, rows_r1, kNb);
-      fetch(f2, L + (int64_t)T * kNb * n + (p + 1) * kNb, n, rows_t0, kNb);
-      fetch(f3, L + (int64_t)(T + 1) * kNb * n + (p + 1) * kNb, n, rows_t1, kNb);
-    }
-    if (mine) {
-      f32x16 acc[2][2] = {};
-#pragma unroll
-      for (int kk = 0; kk < kNb; kk += 2) {
-        float a[2], b[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) a[i] = Ub[qr + 32 * i + l32][kk + h];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) b[j] = Vb[qc + 32 * j + l32][kk + h];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f32(a[i], b[j], acc[i][j]);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) c[i][j][r] -= acc[i][j][r];
-    }
+        for (int r = 0; r < 16; ++r) c[i][j][r] -= acc[i][j][r];
   }
   if (!mine) return;
 #pragma unroll
@@ -428,21 +507,18 @@ __device__ __forceinline__ void trailing_2x2(float* L, int n, int nblk, int p0, 
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = br * kNb + 32 * i + acc_row(r, lane), col = bc * kNb + 32 * j + l32;
-        if (row < n && col < n) L[(int64_t)row * n + col] = c[i][j][r];
-      }
+      for (int r = 0; r < 16; ++r) st1(rb, cof[j], (32 * i + acc_row(r, 0)) * n4, c[i][j][r]);
 }
 
 // The deferred update of a super-panel of kSup panels (p0 .. p0 + kSup - 1): the
 // trailing triangle from block e on (rows r >= t >= e) in 2 x 2 groups.
-__global__ __launch_bounds__(kThreads) void chol_trail_kernel(float* L, int n, int p0, int e, int64_t ws) {
-  __shared__ __attribute__((aligned(16))) Tile tiles[4];
+__global__ __launch_bounds__(kThreads, 2) void chol_trail_kernel(float* L, int n, int p0, int e, int64_t ws) {
+  __shared__ __attribute__((aligned(1024))) char lds[4 * kHalfTile];
   L = at_layer(L, ws, blockIdx.y);
   const int nblk = (n + kNb - 1) / kNb;
   int ti, tj;
   tri_index((int)blockIdx.x, ti, tj);
-  trailing_2x2<kSup>(L, n, nblk, p0, e + 2 * ti, e + 2 * tj, nblk, tiles);
+  trailing_2x2<kSup>(L, n, nblk, p0, e + 2 * ti, e + 2 * tj, nblk, lds);
 }
 
 // Panel-group updates that ride along in a single layer's panel launches (the
@@ -468,9 +544,9 @@ struct CholExtra {
 struct CholWork {
   int kind, R, T, p0, np, t_end;
 };
-__host__ __device__ inline CholWork chol_work_of(int wg, int nblk, int k, int t_end, int split, const CholExtra& ex) {
+__host__ __device__ inline CholWork chol_work_of(int wg, int nblk, int k, int t_end, const CholExtra& ex) {
   CholWork w = {-1, 0, 0, 0, 0, 0};
-  const int m = split == 2 ? nblk - 2 - k : nblk - 1 - k;  // panel-column workgroups of this launch
+  const int m = nblk - 1 - k;  // panel-column workgroups of this launch
   if (ex.trail >= 0 && wg >= m + ex.trail) {
     int idx = wg - m - ex.trail;
     for (int t = 0; t < ex.n_tasks; ++t) {
@@ -500,7 +576,7 @@ __host__ __device__ inline CholWork chol_work_of(int wg, int nblk, int k, int t_
     if (gj < rows) w = CholWork{1, k + 2 + 2 * (gj + idx), k + 2 + 2 * gj, k, 1, t_end};
     return w;
   }
-  w = CholWork{0, k + 1 + (split == 2 ? 1 : 0) + wg, k + 1, k, 1, 0};
+  w = CholWork{0, k + 1 + wg, k + 1, k, 1, 0};
   return w;
 }
 
@@ -511,101 +587,120 @@ __host__ __device__ inline CholWork chol_work_of(int wg, int nblk, int k, int t_
 // column, then run the extra super-panel groups of `x` (none: x.trail = -1).
 // Columns from t_end on receive panel k later, with the rest of its
 // super-panel (chol_trail_kernel, or the extra groups of a later launch).
-// split = 0: every workgroup of the panel column factors the diagonal block
-// itself (no launch waits for another). split = 1: only the diagonal block
-// (one workgroup), which leaves its inverse in Dinv; split = 2: the blocks
-// below it, which read that inverse, and the trailing part. Both forms do the
-// same arithmetic in the same order.
-__global__ __launch_bounds__(kThreads) void chol_step_kernel(float* L, float* Dinv, int n, int k, int t_end,
-                                                            int apply, int split, int* status, int64_t ws,
-                                                            CholExtra ex) {
-  __shared__ __attribute__((aligned(16))) Tile tiles[6];
+// Every workgroup of the panel column factors the diagonal block itself (no
+// launch waits for another): the block's own rows ride through the same
+// elimination, so L_rd needs no inverse and no product after it; the diagonal
+// block's workgroup runs the identity through instead, which leaves the
+// transposed inverse for Dinv.
+__global__ __launch_bounds__(kThreads, 2) void chol_step_kernel(float* L, float* Dinv, int n, int k, int t_end,
+                                                            int apply, int* status, int64_t ws, CholExtra ex) {
+  // the panel's half tiles, then (in their place) the fp32 tiles S and Q
+  __shared__ __attribute__((aligned(1024))) char lds[4 * kHalfTile];
   __shared__ int bad;
   L = at_layer(L, ws, blockIdx.y);
   Dinv = at_layer(Dinv, ws, blockIdx.y);
   status = at_layer(status, ws, blockIdx.y);
   const int nblk = (n + kNb - 1) / kNb;
-  const CholWork wk = chol_work_of((int)blockIdx.x, nblk, k, t_end, split, ex);
+  const CholWork wk = chol_work_of((int)blockIdx.x, nblk, k, t_end, ex);
   if (wk.kind < 0) return;
   if (wk.kind == 1) {
     if (wk.np == 1) {
-      trailing_2x2<1>(L, n, nblk, wk.p0, wk.R, wk.T, wk.t_end, tiles);
+      trailing_2x2<1>(L, n, nblk, wk.p0, wk.R, wk.T, wk.t_end, lds);
     } else {
-      trailing_2x2<kLa>(L, n, nblk, wk.p0, wk.R, wk.T, wk.t_end, tiles);
+      trailing_2x2<kLa>(L, n, nblk, wk.p0, wk.R, wk.T, wk.t_end, lds);
     }
     return;
   }
   apply = apply && k >= 0;
-  Tile &S = tiles[0], &M = tiles[1], &T = tiles[2], &U = tiles[3], &V = tiles[4], &P = tiles[5];
-  const int r = wk.R, t = wk.T;  // block coordinates
-  const int rr = min(kNb, n - r * kNb);
-  float* Lrt = L + (int64_t)r * kNb * n + t * kNb;
-  if (threadIdx.x == 0) bad = 0;
-
-  // next panel column: updated diagonal block, factor, inverse
-  const int d = k + 1;
-  const int nd = min(kNb, n - d * kNb);
+  RowTile &S = *(RowTile*)lds, &Q = *((RowTile*)lds + 1);
+  static_assert(2 * sizeof(RowTile) <= sizeof(lds), "tiles");
+  const int r = wk.R, d = k + 1;  // this workgroup's block row, the panel's column
+  const int rr = min(kNb, n - r * kNb), nd = min(kNb, n - d * kNb);
   const bool off = r != d;
-  Frag fs, fv, ft, fu;
-  if (split == 2) {
-    // below the diagonal block: A_rd - L_rk L_dk^T (the quadrants as the
-    // factor's other waves form them), then times the stored inverse
-    if (apply) fetch(fv, L + (int64_t)d * kNb * n + k * kNb, n, nd, kNb);
-    fetch(ft, Lrt, n, rr, nd);
-    if (apply) fetch(fu, L + (int64_t)r * kNb * n + k * kNb, n, rr, kNb);
-    fetch(fs, Dinv + (int64_t)d * kNb * kNb, kNb, kNb, kNb);
-    if (apply) put(V, fv);
-    put(P, ft);
-    if (apply) put(U, fu);
-    put(M, fs);
-    __syncthreads();
-    if (apply) {
-      const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-      const int r0 = (wave >> 1) * 32, c0 = (wave & 1) * 32;
-      f32x16 acc = {};
-      mma<false, true>(acc, U, r0, 0, V, c0, 0, kNb, lane);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) P[r0 + acc_row(e, lane)][c0 + (lane & 31)] -= acc[e];
-      __syncthreads();
-    }
-    const f32x16 x = quad<false, true>(P, M);
-    __syncthreads();
-    quad_store(P, x, 1.f, false);
-    __syncthreads();
-    store_tile(P, Lrt, n, rr, nd);
-    return;
-  }
-  fetch(fs, L + (int64_t)d * kNb * n + d * kNb, n, nd, nd);
-  if (apply) fetch(fv, L + (int64_t)d * kNb * n + k * kNb, n, nd, kNb);
-  if (off) {
-    fetch(ft, Lrt, n, rr, nd);
-    if (apply) fetch(fu, L + (int64_t)r * kNb * n + k * kNb, n, rr, kNb);
-  }
-  put(S, fs);
-  if (apply) put(V, fv);
-  if (off) {
-    put(P, ft);
-    if (apply) put(U, fu);
-  }
-  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l32 = lane & 31, h = lane >> 5;
+  const int r0 = (wave >> 1) * 32, c0 = (wave & 1) * 32;  // this wave's quadrant of S and Q
+  if (threadIdx.x == 0) bad = 0;
+  const int n4 = n * 4;
+  const __amdgpu_buffer_rsrc_t rd = rows_rsrc(L + (int64_t)d * kNb * n, n, nd);
+  const __amdgpu_buffer_rsrc_t rw = rows_rsrc(L + (int64_t)r * kNb * n, n, off ? rr : 0);
+  Chunk fv[2], fu[2];
+  const int row = threadIdx.x >> 2, chunk = threadIdx.x & 3;
   if (apply) {
-    quad_store(S, quad<false, true>(V, V), -1.f, true);
-    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int o = row * n4 + (k * kNb + 32 * q + chunk * 8) * 4;
+      fetch8(fv[q], rd, o);
+      fetch8(fu[q], rw, o);
+    }
   }
-  // factor the diagonal block; an off-diagonal workgroup's other waves form
-  // A_rd - L_rk L_dk^T meanwhile
-  factor64(S, M, T, nd, &bad, off && apply ? &P : nullptr, &U, &V);
-  if (!off) {
-    store_tile(M, Dinv + (int64_t)d * kNb * kNb, kNb, kNb, kNb);
-    if (threadIdx.x == 0 && bad) atomicOr(status, 1);
+  // the quadrants in the accumulator layout; past the matrix S is the identity
+  // (which keeps the factorisation defined) and Q zero
+  float vs[16], vq[16];
+  const int cof = c0 + l32 < nd ? (r0 + 4 * h) * n4 + (d * kNb + c0 + l32) * 4 : kNoCol;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    vs[e] = ld1(rd, cof, acc_row(e, 0) * n4);
+    vq[e] = ld1(rw, cof, acc_row(e, 0) * n4);
+  }
+  if (apply) {
+    // A_dd - L_dk L_dk^T and A_rd - L_rk L_dk^T
+    char *lv = lds, *lu = lds + 2 * kHalfTile;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      put8(lv + q * kHalfTile, fv[q], row, chunk);
+      put8(lu + q * kHalfTile, fu[q], row, chunk);
+    }
+    __syncthreads();
+    f32x16 as = {}, aq = {};
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      bf16x8 a[3], b[3], u[3];
+      read3(a, lv + (kk >> 1) * kHalfTile, r0 + l32, 2 * (kk & 1) + h);
+      read3(b, lv + (kk >> 1) * kHalfTile, c0 + l32, 2 * (kk & 1) + h);
+      read3(u, lu + (kk >> 1) * kHalfTile, r0 + l32, 2 * (kk & 1) + h);
+      mma6(as, a, b);
+      mma6(aq, u, b);
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      vs[e] -= as[e];
+      vq[e] -= aq[e];
+    }
+    __syncthreads();  // the half tiles are read
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int i = r0 + acc_row(e, lane), j = c0 + l32;
+    const float one = i == j ? 1.f : 0.f;
+    const float v = i < nd && j < nd ? vs[e] : one;
+    if (i >= j) {  // the lower part, mirrored
+      S[i][j] = v;
+      S[j][i] = v;
+    }
+    Q[i][j] = off ? vq[e] : one;
+  }
+  __syncthreads();
+  factor_rows(S, Q, &bad);
+  if (off) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = threadIdx.x + q * kThreads;
+      const int i = e >> 4, j = (e & 15) * 4;
+      const f32x4 v = *(const f32x4*)&Q[i][j];
+      const int o = j < nd ? i * n4 + (d * kNb + j) * 4 : kNoCol;
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rw, o, 0, 0);
+    }
     return;
   }
-  // L_rd = (A_rd - L_rk L_dk^T) . M^T
-  const f32x16 x = quad<false, true>(P, M);
-  __syncthreads();
-  quad_store(P, x, 1.f, false);
-  __syncthreads();
-  store_tile(P, Lrt, n, rr, nd);
+  float* D = Dinv + (int64_t)d * kNb * kNb;  // L^-1 = Q^T
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = threadIdx.x + q * kThreads;
+    const int i = e >> 4, j = (e & 15) * 4;
+    *(f32x4*)(D + i * kNb + j) = f32x4{Q[j][i], Q[j + 1][i], Q[j + 2][i], Q[j + 3][i]};
+  }
+  if (threadIdx.x == 0 && bad) atomicOr(status, 1);
 }
 
 // ---------------------------------------------------------------- 256-block
@@ -963,30 +1058,6 @@ struct SplitArgs {
   int64_t ldb, lb;  // lb: bytes per layer of B
 };
 
-typedef unsigned int u32;
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-// x[0..7] cut into three bf16 chunks of 8
-__device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&p)[3]) {
-  // (-1, 0) and (0, -1) as packed bf16, kept out of the compiler's sight: as an
-  // inline constant of a packed operand -1.0 is taken for the wrong half
-  u32 lo = 0x0000bf80u, hi = 0xbf800000u;
-  asm("" : "+s"(lo), "+s"(hi));
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    float a = x[2 * j], b = x[2 * j + 1];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const bf16x2 w = __builtin_convertvector((f32x2{a, b}), bf16x2);
-      p[q][j] = __builtin_bit_cast(u32, w);
-      if (q < 2) {  // what the part left: one multiply-add with the pair, exact
-        a = __builtin_amdgcn_fdot2_f32_bf16(w, __builtin_bit_cast(bf16x2, lo), a, false);
-        b = __builtin_amdgcn_fdot2_f32_bf16(w, __builtin_bit_cast(bf16x2, hi), b, false);
-      }
-    }
-  }
-}
-
 // One side of the tile: T rows of the LDS planes (the m or n index), KS k; every
 // thread holds one chunk of 8 k of one row. KM: k is the row of the source,
 // else the column.
@@ -1090,18 +1161,17 @@ __global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(Sp
   float* C = at_layer(jb.C, jb.lc, layer);
   const float* Cin = at_layer(jb.Cin, jb.lc, layer);
 
-  // the minuend through a descriptor that ends at the job's last element: rows
-  // past M read zero, columns past N neighbours that are not stored
+  // the minuend and the result: rows past M read zero and are not stored
   float cin[Q][Q][16];
-  __amdgpu_buffer_rsrc_t rc;
-  int coff;
-  {
-    int64_t nrec = jb.Cin != nullptr ? ((int64_t)(M - m0 - 1) * jb.ldc + (N - n0)) * 4 : 0;
-    if (nrec > 0x7fffffff) nrec = 0x7fffffff;
-    rc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Cin + (int64_t)m0 * jb.ldc + n0), 0, (int)nrec, 0x00020000);
-    coff = (int)(((wm0 + 4 * h) * jb.ldc + wn0 + l32) * 4);
-  }
+  const __amdgpu_buffer_rsrc_t ro = rows_rsrc(C + (int64_t)m0 * jb.ldc, jb.ldc, M - m0);
+  const __amdgpu_buffer_rsrc_t rc = rows_rsrc(Cin + (int64_t)m0 * jb.ldc, jb.ldc, jb.Cin != nullptr ? M - m0 : 0);
   const int ldc4 = (int)(jb.ldc * 4);
+  int cof[Q];
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    const int col = n0 + wn0 + 32 * j + l32;
+    cof[j] = col < N ? (wm0 + 4 * h) * ldc4 + col * 4 : kNoCol;
+  }
 
   const int steps = (K + kKs - 1) / kKs;
   sa.load(0);
@@ -1124,8 +1194,7 @@ __global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(Sp
         for (int j = 0; j < Q; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            cin[i][j][r] = __builtin_bit_cast(float, (u32)__builtin_amdgcn_raw_buffer_load_b32(
-                rc, coff + 128 * j, (32 * i + 8 * (r >> 2) + (r & 3)) * ldc4, 0));
+            cin[i][j][r] = ld1(rc, cof[j], (32 * i + acc_row(r, 0)) * ldc4);
     }
 #pragma unroll
     for (int kk = 0; kk < kKs / 16; ++kk) {
@@ -1165,17 +1234,11 @@ __global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(Sp
 #pragma unroll
   for (int i = 0; i < Q; ++i)
 #pragma unroll
-    for (int j = 0; j < Q; ++j) {
-      const int col = n0 + wn0 + 32 * j + l32;
+    for (int j = 0; j < Q; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = m0 + wm0 + 32 * i + acc_row(r, lane);
-        if (row < M && col < N) {
-          const int64_t o = (int64_t)row * jb.ldc + col;
-          C[o] = jb.Cin != nullptr ? cin[i][j][r] - acc[i][j][r] : acc[i][j][r];
-        }
-      }
-    }
+      for (int r = 0; r < 16; ++r)
+        st1(ro, cof[j], (32 * i + acc_row(r, 0)) * ldc4,
+            jb.Cin != nullptr ? cin[i][j][r] - acc[i][j][r] : acc[i][j][r]);
 }
 
 }  // namespace
@@ -1333,7 +1396,7 @@ int solve_lookahead_check(int nblk, int n_cu) {
       return true;
     };
     for (int wg = 0; wg < plan.grid[k + 1]; ++wg) {
-      const CholWork w = chol_work_of(wg, nblk, k, plan.t_end[k + 1], 0, plan.extra[k + 1]);
+      const CholWork w = chol_work_of(wg, nblk, k, plan.t_end[k + 1], plan.extra[k + 1]);
       if (w.kind == 0) {
         if (!receive(w.R, w.T, k, k >= 0 ? 1 : 0)) return fail;
       } else if (w.kind == 1) {
@@ -1354,8 +1417,8 @@ int solve_lookahead_check(int nblk, int n_cu) {
 }
 
 // A single layer's factorisation in the look-ahead form (below) from 48
-// panels on (measured: 80 panels 5.07 -> 4.74 ms per solve, 48 panels 1.76 ->
-// 1.70 ms, 24 panels 0.654 -> 0.656 ms); ISPA_SOLVE_LOOKAHEAD=0 / 1 switches
+// panels on (measured: 80 panels 3.38 -> 3.30 ms per solve, 24 panels 0.517 ->
+// 0.526 ms); ISPA_SOLVE_LOOKAHEAD=0 / 1 switches
 // it off / on at every size.
 static bool solve_lookahead(int nblk) {
   if ((nblk - 2) / kLa + 1 >= kMaxTasks) return false;  // bands beyond the task table
@@ -1403,18 +1466,18 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
     // every task whose deadline it is, then more of its available tasks,
     // earliest deadline first, as many as fill the rounds of workgroups on
     // the chip that the launch needs anyway (one at least). A task's
-    // workgroup (two panels on a 2 x 2 group of blocks, ~18.5 us) takes a
-    // little longer than the launch's panel chain (~15.5 us); with groups of
-    // four panels it took ~26 us (at 80 panels: 4.93 ms per solve, against
-    // 4.74 ms with groups of two and 5.07 ms without look-ahead). Each block
-    // still receives every panel once, in panel order, with the same
+    // workgroup (two panels on a 2 x 2 group of blocks, ~15 us) takes longer
+    // than the launch's panel chain (~10.5 us), so groups of more panels would
+    // stretch the launches further; two rounds of workgroups per launch (two
+    // fit on a compute unit) took 3.34 ms per solve at 80 panels, one round
+    // 3.30. Each block still receives every panel once, in panel order, with the same
     // arithmetic: bit for bit the factor of the other forms.
     const int n_cu = attn_cu_count() > 0 ? attn_cu_count() : 256;
     LookaheadPlan plan;
     lookahead_plan(nblk, n_cu, &plan);
     for (int k = -1; k <= nblk - 2; ++k)
       hipLaunchKernelGGL(chol_step_kernel, dim3(plan.grid[k + 1], 1), dim3(kThreads), 0, stream, L, w.dinv, d, k,
-                         plan.t_end[k + 1], k >= 0 ? 1 : 0, 0, w.status, ws, plan.extra[k + 1]);
+                         plan.t_end[k + 1], k >= 0 ? 1 : 0, w.status, ws, plan.extra[k + 1]);
   } else {
     const int c_def = nl > 1 ? nblk + sup : 0;
     for (int k = -1; k <= nblk - 2; ++k) {
@@ -1438,18 +1501,8 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
       const int rows = (nblk - k - 2 + 1) / 2;      // group rows of the trailing part
       const int cols = k >= 0 && t_end > k + 2 ? (t_end - k - 2 + 1) / 2 : 0;  // launch -1 has no panel to apply
       const int groups = cols * rows - cols * (cols - 1) / 2;
-      if (nl == 1) {
-        hipLaunchKernelGGL(chol_step_kernel, dim3(m + groups, nl), dim3(kThreads), 0, stream, L, w.dinv, d, k, t_end,
-                           apply, 0, w.status, ws, none);
-      } else {
-        // with many layers the diagonal block is factored once per layer, in its
-        // own launch, rather than once per block of the column
-        hipLaunchKernelGGL(chol_step_kernel, dim3(1, nl), dim3(kThreads), 0, stream, L, w.dinv, d, k, t_end, apply, 1,
-                           w.status, ws, none);
-        if (m - 1 + groups > 0)
-          hipLaunchKernelGGL(chol_step_kernel, dim3(m - 1 + groups, nl), dim3(kThreads), 0, stream, L, w.dinv, d, k,
-                             t_end, apply, 2, w.status, ws, none);
-      }
+      hipLaunchKernelGGL(chol_step_kernel, dim3(m + groups, nl), dim3(kThreads), 0, stream, L, w.dinv, d, k, t_end,
+                         apply, w.status, ws, none);
     }
   }
   // X_I, P_I = X_I^T X_I, Lh below the 256-block diagonal

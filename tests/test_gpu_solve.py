@@ -43,6 +43,33 @@ def test_solve_matches_oracle_ragged(d_in, d_out, n):
     assert rel_fro(f64(dw2), oracle.solve_modulation(ref.G, ref.C, 2 * lam)) <= DW_TOL
 
 
+@pytest.mark.parametrize("d", [8, 16, 24, 56, 64, 72, 120, 136, 208])
+def test_solve_panel_edges(d):
+    # the factorisation eliminates 16 columns at a time inside 64-wide panels:
+    # sizes that end inside or at the end of a 16-column piece and of a panel,
+    # channels of scales 1 to 1e-3 (pivots over six orders of magnitude), and a
+    # channel without energy, whose zero pivot must be reported wherever it is
+    n, lam = 3 * d + 40, 1e-6
+    x = (rows(44, d, n, d, torch.float32) * torch.logspace(0, -3, d, device=DEV)).to(torch.bfloat16)
+    y = synth.normal((n, 8), synth.seed_of(44, d, synth.Y_FULL), DEV, dtype=torch.float32)
+    st = ispa.Stats(d, 8, max_rows=n, device=DEV)
+    st.accum(x, y, torch.zeros_like(y))
+    dw, _ = st.solve(lam)
+    G, C, _, _ = st.views()
+    g = np.tril(f64(G))
+    g, s = g + np.tril(g, -1).T, np.logspace(0, 3, d)
+    # a column's error scales with its channel: compare what the channel adds
+    ref = oracle.solve_modulation(g, f64(C), float(np.float32(lam)))
+    assert rel_fro(f64(dw) / s[:, None], ref / s[:, None]) <= 1e-5
+    for col in {0, d // 2, d - 1}:
+        z = x.clone()
+        z[:, col] = 0
+        st.reset()
+        st.accum(z, y, torch.zeros_like(y))
+        with pytest.raises(ispa.NotSPDError):
+            st.solve(0.0)
+
+
 def test_not_spd_reported():
     d, n = 64, 80
     x = rows(31, 0, n, d)
