@@ -17,6 +17,7 @@ works without the library, but every call raises if it is not built.
 """
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -118,14 +119,25 @@ def _check(status, where):
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
+
+
+# the current stream's handle without building a torch.cuda.Stream (about 3 us of
+# a call whose kernel takes 10)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    if _raw_stream is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _require(t, name, dtype, device=None, ndim=2):
+    # one expression for the usual case; the reasons only when it fails
+    if (isinstance(t, torch.Tensor) and t.dtype == dtype and t.is_cuda and t.dim() == ndim and t.is_contiguous()
+            and (device is None or t.device == device)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
@@ -138,16 +150,11 @@ def _require(t, name, dtype, device=None, ndim=2):
         raise ValueError(f"{name} must be a contiguous {ndim}-d tensor")
 
 
-_workspaces = {}
-
-
-def _workspace(device, nbytes):
-    """A cached device workspace of at least nbytes (grown on demand)."""
-    ws = _workspaces.get(device)
-    if ws is None or ws.numel() < nbytes:
-        ws = torch.empty(((nbytes + 255) // 256) * 256, dtype=torch.uint8, device=device)
-        _workspaces[device] = ws
-    return ws
+@functools.lru_cache(maxsize=512)
+def _attn_workspace_bytes(index, *sizes):
+    """ispa_attn_workspace_bytes on device `index`: a function of the sizes alone."""
+    with torch.cuda.device(index):
+        return lib().ispa_attn_workspace_bytes(*sizes)
 
 
 def _qkv(q, k_cache, v_cache, n_heads):
@@ -163,30 +170,27 @@ def _qkv(q, k_cache, v_cache, n_heads):
     return dev, n_q, hidden, hidden // n_heads
 
 
-def _outputs(dev, n_q, hidden, n_heads, pairs):
-    for name, t, shape in pairs:
-        if t is not None:
-            _require(t, name, torch.float32, dev)
-            if tuple(t.shape) != shape:
-                raise ValueError(f"{name} must have shape {shape}")
+def _output(t, name, like, shape):
+    """The caller's output t, checked, or a new fp32 tensor of that shape on like's device."""
+    if t is None:
+        return like.new_empty(shape, dtype=torch.float32)
+    _require(t, name, torch.float32, like.device)
+    if tuple(t.shape) != shape:
+        raise ValueError(f"{name} must have shape {shape}")
+    return t
 
 
 def _chunk_outputs(q, k_cache, v_cache, cache_len, n_heads, dual, out, lse, out_local, lse_local, need_lse):
     dev, n_q, hidden, head_dim = _qkv(q, k_cache, v_cache, n_heads)
     if k_cache.shape[0] < cache_len or v_cache.shape[0] < cache_len:
         raise ValueError("cache tensors hold fewer than cache_len rows")
-    if out is None:
-        out = torch.empty((n_q, hidden), dtype=torch.float32, device=dev)
-    if lse is None and need_lse:
-        lse = torch.empty((n_heads, n_q), dtype=torch.float32, device=dev)
-    if dual:
-        if out_local is None:
-            out_local = torch.empty((n_q, hidden), dtype=torch.float32, device=dev)
-        if lse_local is None and need_lse:
-            lse_local = torch.empty((n_heads, n_q), dtype=torch.float32, device=dev)
-    _outputs(dev, n_q, hidden, n_heads,
-             (("out", out, (n_q, hidden)), ("out_local", out_local, (n_q, hidden)),
-              ("lse", lse, (n_heads, n_q)), ("lse_local", lse_local, (n_heads, n_q))))
+    out = _output(out, "out", q, (n_q, hidden))
+    if dual or out_local is not None:
+        out_local = _output(out_local, "out_local", q, (n_q, hidden))
+    if lse is not None or need_lse:
+        lse = _output(lse, "lse", q, (n_heads, n_q))
+    if lse_local is not None or (dual and need_lse):
+        lse_local = _output(lse_local, "lse_local", q, (n_heads, n_q))
     return dev, n_q, hidden, head_dim, out, lse, out_local, lse_local
 
 
@@ -198,19 +202,19 @@ def attn_chunk(q, k_cache, v_cache, cache_len, window, n_heads, sink_len=0, scal
     Returns (out, lse), or (out, lse, out_local, lse_local) when dual: out is then
     the full-cache result and out_local the sink + window result. ``segments``:
     0 splits the work over the chip when whole work items fill it poorly, < 0
-    never splits, > 0 forces that many runs (the workspace is cached per device).
+    never splits, > 0 forces that many runs.
     """
     L = lib()
     dev, n_q, hidden, head_dim, out, lse, out_local, lse_local = _chunk_outputs(
         q, k_cache, v_cache, cache_len, n_heads, dual, out, lse, out_local, lse_local, need_lse)
-    with torch.cuda.device(dev):
-        nbytes = L.ispa_attn_workspace_bytes(int(cache_len), int(window), int(sink_len), int(n_q), int(n_heads),
-                                             int(head_dim), int(bool(dual)), int(segments))
-    ws = _workspace(dev, nbytes) if nbytes > 0 else None
-    st = L.ispa_attn_chunk_ws(_ptr(q), _ptr(k_cache), _ptr(v_cache), int(cache_len), int(window), int(sink_len),
-                              int(n_q), int(n_heads), int(head_dim), float(scale), _ptr(out), _ptr(lse),
-                              _ptr(out_local if dual else None), _ptr(lse_local if dual else None),
-                              int(segments), _ptr(ws), int(ws.numel() if ws is not None else 0), _stream(dev))
+    sizes = (int(cache_len), int(window), int(sink_len), n_q, int(n_heads), head_dim, int(bool(dual)), int(segments))
+    nbytes = _attn_workspace_bytes(dev.index, *sizes)
+    # from the caching allocator, on the current stream: calls on other streams
+    # and threads have workspaces of their own
+    ws = q.new_empty(nbytes, dtype=torch.uint8) if nbytes > 0 else None
+    st = L.ispa_attn_chunk_ws(q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), *sizes[:6], float(scale),
+                              out.data_ptr(), _ptr(lse), _ptr(out_local if dual else None),
+                              _ptr(lse_local if dual else None), sizes[7], _ptr(ws), nbytes, _stream(dev))
     _check(st, "ispa_attn_chunk_ws")
     return (out, lse, out_local, lse_local) if dual else (out, lse)
 
@@ -243,11 +247,8 @@ def attn_ranges(q, k_cache, v_cache, ranges, n_heads, scale=0.0, out=None, lse=N
     for b, e in ranges:
         if not (0 <= b < e) or e > k_cache.shape[0] or e > v_cache.shape[0]:
             raise ValueError(f"key range {(b, e)} is empty or outside the cache tensors")
-    if out is None:
-        out = torch.empty((n_q, hidden), dtype=torch.float32, device=dev)
-    if lse is None:
-        lse = torch.empty((n_heads, n_q), dtype=torch.float32, device=dev)
-    _outputs(dev, n_q, hidden, n_heads, (("out", out, (n_q, hidden)), ("lse", lse, (n_heads, n_q))))
+    out = _output(out, "out", q, (n_q, hidden))
+    lse = _output(lse, "lse", q, (n_heads, n_q))
     arr = (_c_i64 * max(1, 2 * len(ranges)))(*[v for r in ranges for v in r])
     st = L.ispa_attn_ranges(_ptr(q), _ptr(k_cache), _ptr(v_cache), arr, len(ranges), int(n_q), int(n_heads),
                             int(head_dim), float(scale), _ptr(out), _ptr(lse), _stream(dev))
@@ -270,11 +271,8 @@ def attn_merge(out_a, lse_a, out_b, lse_b, out=None, lse=None):
         _require(t, name, torch.float32, dev)
         if tuple(t.shape) != shape:
             raise ValueError(f"{name} must have shape {shape}")
-    if out is None:
-        out = torch.empty((n_q, hidden), dtype=torch.float32, device=dev)
-    if lse is None:
-        lse = torch.empty((n_heads, n_q), dtype=torch.float32, device=dev)
-    _outputs(dev, n_q, hidden, n_heads, (("out", out, (n_q, hidden)), ("lse", lse, (n_heads, n_q))))
+    out = _output(out, "out", out_a, (n_q, hidden))
+    lse = _output(lse, "lse", out_a, (n_heads, n_q))
     st = L.ispa_attn_merge(_ptr(out_a), _ptr(lse_a), _ptr(out_b), _ptr(lse_b), int(n_q), int(n_heads),
                            int(hidden // n_heads), _ptr(out), _ptr(lse), _stream(dev))
     _check(st, "ispa_attn_merge")
@@ -547,7 +545,7 @@ def project(a, weight, out=None, out_dtype=torch.float32):
     if k != d_in:
         raise ValueError("weight must be [d_out, d_in] with the d_in of a")
     if out is None:
-        out = torch.empty((n, d_out), dtype=out_dtype, device=a.device)
+        out = a.new_empty((n, d_out), dtype=out_dtype)
     if out.dtype not in _DT:
         raise TypeError("out must be fp32 or bf16")
     _require(out, "out", out.dtype, a.device)
@@ -568,9 +566,9 @@ def quantize_rows(x, q=None, scale=None):
     _require(x, "x", x.dtype)
     rows, cols = x.shape
     if q is None:
-        q = torch.empty((rows, cols), dtype=torch.int8, device=x.device)
+        q = x.new_empty((rows, cols), dtype=torch.int8)
     if scale is None:
-        scale = torch.empty((rows,), dtype=torch.float32, device=x.device)
+        scale = x.new_empty((rows,), dtype=torch.float32)
     _require(q, "q", torch.int8, x.device)
     _require(scale, "scale", torch.float32, x.device, ndim=1)
     if tuple(q.shape) != (rows, cols) or scale.shape[0] != rows:
@@ -594,7 +592,7 @@ def project_w8a8(q_a, scale_a, q_w, scale_w, out=None, out_dtype=torch.float32):
     if k != d_in or scale_a.shape[0] != n or scale_w.shape[0] != d_out:
         raise ValueError("q_w must be [d_out, d_in], scale_a [n] and scale_w [d_out]")
     if out is None:
-        out = torch.empty((n, d_out), dtype=out_dtype, device=dev)
+        out = q_a.new_empty((n, d_out), dtype=out_dtype)
     if out.dtype not in _DT:
         raise TypeError("out must be fp32 or bf16")
     _require(out, "out", out.dtype, dev)
