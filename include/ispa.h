@@ -112,15 +112,16 @@ int ispa_attn_chunk(const void* q, const void* k_cache, const void* v_cache,
  * blocks = 228 work items on 256 compute units). Split, every workgroup takes
  * an equal run of (work item, 64-key tile) units; runs that end inside a work
  * item leave a normalised partial output and LSE in the workspace, combined
- * with Eq. 11-12 in run order. At head_dim 128 the run that completes a work
- * item combines them inside the same kernel (the runs count themselves on
- * per-item counters in the workspace, which the call clears first); at
- * head_dim 64 a merge kernel combines them after the launch. The results
- * agree with ispa_attn_chunk within rounding (the merge reassociates the
- * softmax sums) and do not depend on which run finishes last.
+ * with Eq. 11-12 in run order, by a merge kernel after the launch or, at
+ * head_dim 128 where that is faster, by the run that completes a work item (the
+ * runs count themselves on per-item counters in the workspace, which the call
+ * clears first). The results agree with ispa_attn_chunk within rounding (the
+ * merge reassociates the softmax sums) and do not depend on which run finishes
+ * last.
  *
  *   segments   < 0: never split (exactly ispa_attn_chunk)
  *              0:   split when whole work items would fill the device poorly
+ *                   and the gain repays the partial results (small calls too)
  *              > 0: split into exactly this many runs (at most the number of
  *                   units)
  *   workspace  device, 256-byte aligned, at least ispa_attn_workspace_bytes

@@ -63,8 +63,6 @@ static_assert(kBq == kAttnBq, "work item size");
 constexpr int kBk = 64;                // keys per tile
 constexpr int kXcds = 8;
 constexpr float kLazyLog2 = 8.f;       // rescale threshold of the softmax reference
-constexpr int kSplitMinTiles = 384;    // automatic split only from this many key tiles per item
-constexpr int kSplitFillPct = 85;      // automatic split only below this fill of the last round
 
 template <int D>
 struct Cfg {
@@ -721,7 +719,69 @@ int attn_cu_count() {
   return n;
 }
 
+namespace {
+
+// The automatic split: how many segments (0: whole work items) for n_work items
+// of T tiles each on n_cu compute units, one workgroup on each.
+//
+// Up to one item per compute unit the choice is the smallest estimate in
+// microseconds of: whole items; every item cut into k equal pieces, all resident
+// at once; n_cu equal runs over item boundaries. A tile costs more the fuller
+// the chip is (its power limit) and more in runs (they walk a head's keys at two
+// offsets, which the L2 bridges less well); pieces pay the partial results'
+// traffic and the merge kernel. Fitted to, and choosing as, sweeps of items,
+// tiles and pieces (measured whole -> chosen, us): head_dim 128: 84 items of 147
+// tiles 181 -> 101 (3 pieces), 84 of 25 41 -> 41 (whole), 60 of 47 66 -> 43 (4),
+// 12 of 74 95 -> 32 (12), 4 of 32 46 -> 23 (8), 1 of 512 588 -> 42 (32), 76 of
+// 512 597 -> 278 (3), 190 of 512 686 -> 652 (runs), 210 of 147 213 (whole; runs
+// 230), 228 of 512 whole (runs 3% slower); head_dim 64: 168 of 98 145 -> 112
+// (runs), 24 of 74 109 -> 28 (8), 64 of 19 33 -> 26 (4).
+// With more items than compute units the last round's fill decides, from 384
+// tiles on, where the launch is long enough to repay it: runs below 85%.
+int64_t auto_segments(int64_t n_work, int T, int n_cu, int head_dim, bool dual) {
+  if (n_work > n_cu) {
+    const int64_t rounds = (n_work + n_cu - 1) / n_cu;
+    return T < 384 || n_work * 100 >= rounds * n_cu * 85 ? 0 : n_cu;
+  }
+  const bool d128 = head_dim == 128;
+  const double tile = d128 ? 1.15 : 1.30, full = d128 ? 0.35 : 0.15;  // per tile, and more on a full chip
+  const double run_tile = d128 ? 1.65 : 1.50, fixed = d128 ? 8.0 : 6.0, merge = dual ? 12.0 : 7.0;
+  const double piece = (d128 ? 0.065 : 0.033) * (dual ? 1.5 : 1.0);  // a piece's partial written and read
+  auto aligned = [&](int64_t k) {
+    const double t = (double)((T + k - 1) / k) * (tile + full * (double)(n_work * k) / n_cu) + fixed;
+    return k == 1 ? t : t + merge + piece * (double)(n_work * k) + 0.25 * (double)k;
+  };
+  int64_t seg = 0;
+  double best = aligned(1);
+  for (int64_t k = 2; k <= 32 && n_work * k <= n_cu && T / k >= 4; ++k) {
+    if (aligned(k) < best) {
+      best = aligned(k);
+      seg = n_work * k;
+    }
+  }
+  const int64_t U = n_work * T;
+  if (U / n_cu >= 16) {
+    const double t = (double)U / n_cu * run_tile + fixed + merge + piece * (double)(n_cu + n_work);
+    if (t < best) seg = n_cu;
+  }
+  return seg;
+}
+
+// Whether a split launch of the head_dim-128 kernel completes its work items
+// itself: forced splits (unless ISPA_ATTN_MERGE_KERNEL=1), and automatic ones of
+// dual-stream calls of many items, whose two partial results per piece cost the
+// merge kernel more (10 heads of 4680 queries: 661 against 670 us; single-stream
+// calls: 655 against 651, six heads 409 against 398, small ones 69 against 33).
+bool split_folds(const AttnArgs& a) {
+  if (a.split.n_seg == 0 || a.split.ctr == nullptr || !a.split.fold) return false;
+  const char* env = getenv("ISPA_ATTN_MERGE_KERNEL");
+  return !(env != nullptr && env[0] == '1');
+}
+
+}  // namespace
+
 size_t attn_plan_split(const AttnArgs& a, int head_dim, int segments, AttnSplit* s) {
+  s->fold = false;
   s->units = 0;
   s->n_seg = 0;
   s->max_pieces = 0;
@@ -736,23 +796,13 @@ size_t attn_plan_split(const AttnArgs& a, int head_dim, int segments, AttnSplit*
   int64_t G;
   if (segments > 0) {
     G = segments;
+    s->fold = true;
   } else {
-    // whole work items per workgroup leave a fraction of the last round of
-    // workgroups idle; split only when that fraction is large and the launch
-    // is long enough to repay the partial results' traffic and the merge.
-    // The chip runs these launches at its power limit, where idle compute
-    // units let the busy ones clock higher: 228 items on 256 CUs (89% full)
-    // take as long whole as split, with 40% fewer HBM bytes; at 82% and
-    // below the split is faster (ISPA_ATTN_SPLIT_FILL overrides the percent)
     const int n_cu = attn_cu_count();
-    if (n_cu <= 0 || T < kSplitMinTiles) return 0;
-    const int64_t rounds = (n_work + n_cu - 1) / n_cu;
-    const char* fill_env = getenv("ISPA_ATTN_SPLIT_FILL");
-    const int fill_pct = fill_env != nullptr ? atoi(fill_env) : kSplitFillPct;
-    if (n_work * 100 >= rounds * n_cu * fill_pct) return 0;
-    G = n_cu;
-    if (U / G < 16) G = U / 16;
+    const bool dual = a.r.n_total > a.r.n_local;
+    G = n_cu > 0 ? auto_segments(n_work, T, n_cu, head_dim, dual) : 0;
     if (G < 2) return 0;
+    s->fold = dual && 2 * n_work > n_cu;
   }
   if (G > U) G = U;
   if (G > (1 << 20)) G = 1 << 20;
@@ -761,7 +811,8 @@ size_t attn_plan_split(const AttnArgs& a, int head_dim, int segments, AttnSplit*
   const int64_t seg_max = (U + G - 1) / G;
   s->units = U;
   s->n_seg = (int32_t)G;
-  s->max_pieces = (int32_t)((seg_max + T - 1) / T + 1);
+  // a whole number of segments per item ends with it: one piece per segment
+  s->max_pieces = G % n_work == 0 ? 1 : (int32_t)((seg_max + T - 1) / T + 1);
   const size_t slots = (size_t)G * s->max_pieces * 2 * kBq;
   s->lse_offset = (slots * head_dim * 4 + 255) / 256 * 256;
   s->ctr_offset = (s->lse_offset + slots * 4 + 255) / 256 * 256;
@@ -776,15 +827,13 @@ hipError_t launch_attn_chunk(const AttnArgs& a, int head_dim, hipStream_t stream
   const int grid = per_xcd * kXcds;
   hipError_t e;
   if (attn_fast_eligible(a, head_dim)) {
-    // split: the pieces complete their work items (counters cleared first);
-    // no merge kernel (ISPA_ATTN_MERGE_KERNEL=1: the merge kernel instead)
-    const char* env = getenv("ISPA_ATTN_MERGE_KERNEL");
-    if (a.split.n_seg > 0 && a.split.ctr != nullptr && !(env != nullptr && env[0] == '1')) {
+    const bool fold = split_folds(a);  // the pieces complete their work items (counters cleared first)
+    if (fold) {
       e = launch_zero(a.split.ctr, (size_t)n_work * 2 * 4 * sizeof(uint32_t), stream);
       if (e != hipSuccess) return e;
-      return launch_attn_fast(a, stream);
     }
-    e = launch_attn_fast(a, stream);
+    e = launch_attn_fast(a, fold, stream);
+    if (fold) return e;
   } else {
     if (head_dim == 128) {
       hipLaunchKernelGGL(attn_chunk_kernel<128>, dim3(grid), dim3(kThreads), 0, stream, a, q_tiles);

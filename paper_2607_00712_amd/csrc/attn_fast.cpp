@@ -100,7 +100,7 @@ bool attn_fast_eligible(const AttnArgs& a, int head_dim) {
   return fast_function() != nullptr;
 }
 
-hipError_t launch_attn_fast(const AttnArgs& a, hipStream_t stream) {
+hipError_t launch_attn_fast(const AttnArgs& a, bool fold, hipStream_t stream) {
   hipFunction_t fn = fast_function();
   if (fn == nullptr) return hipErrorNotFound;
   int n_local = 0;
@@ -147,8 +147,7 @@ hipError_t launch_attn_fast(const AttnArgs& a, hipStream_t stream) {
   p.neg_scale_log2 = -a.scale_log2;
   p.ld2 = (int32_t)(a.ld * 2);
   p.ld4 = (int32_t)(a.ld * 4);
-  const char* env = getenv("ISPA_ATTN_MERGE_KERNEL");
-  p.ctr = a.split.n_seg > 0 && !(env != nullptr && env[0] == '1') ? a.split.ctr : nullptr;
+  p.ctr = fold ? a.split.ctr : nullptr;
   size_t size = sizeof(p);
   void* config[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, &p, HIP_LAUNCH_PARAM_BUFFER_SIZE, &size, HIP_LAUNCH_PARAM_END};
   return hipModuleLaunchKernel(fn, (unsigned)(per_xcd * 8), 1, 1, 256, 1, 1, 0, stream, nullptr, config);

@@ -48,6 +48,7 @@ struct AttnSplit {
   // kernel's pieces complete their work items themselves); null: the merge
   // kernel completes them after the launch
   uint32_t* ctr;
+  bool fold;  // the assembly kernel completes the items (else the merge kernel)
   size_t lse_offset, ctr_offset;  // byte offsets of part_lse and ctr in the workspace
 };
 constexpr int kAttnBq = 256;  // queries per work item
@@ -80,9 +81,10 @@ size_t attn_plan_split(const AttnArgs& a, int head_dim, int segments, AttnSplit*
 hipError_t launch_attn_chunk(const AttnArgs& a, int head_dim, hipStream_t stream);
 // The hand-scheduled head_dim-128 kernel (attn_fast.cpp): whether it takes
 // this launch (its 32-bit work arithmetic fits and its code object loaded on
-// the current device), and the launch itself (the split's merge excluded).
+// the current device), and the launch itself (fold: a split launch completes its
+// work items; else its merge is the caller's).
 bool attn_fast_eligible(const AttnArgs& a, int head_dim);
-hipError_t launch_attn_fast(const AttnArgs& a, hipStream_t stream);
+hipError_t launch_attn_fast(const AttnArgs& a, bool fold, hipStream_t stream);
 // out = 0, lse = -inf (attention over an empty key set)
 hipError_t launch_attn_empty(float* out, float* lse, int64_t n_q, int64_t n_heads, int head_dim,
                              hipStream_t stream);

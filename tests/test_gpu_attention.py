@@ -8,7 +8,7 @@ import torch
 import oracle
 import synth
 import paper_2607_00712_amd as ispa
-from parity_util import assert_attn, assert_lse, f64
+from parity_util import ATTN_TOL, assert_attn, assert_lse, attn_err, f64
 
 pytestmark = pytest.mark.gpu
 
@@ -163,6 +163,55 @@ def test_automatic_split_choice():
         assert L.ispa_attn_workspace_bytes(32760, 9360, 0, 4680, 12, 128, 1, 0) == 0
         assert L.ispa_attn_workspace_bytes(32760, 9360, 0, 4680, 10, 128, 1, 0) > 0
     assert L.ispa_attn_workspace_bytes(32760, 9360, 0, 4680, 10, 128, 1, -1) == 0
+
+
+# calls that the automatic split cuts: equal pieces of every item (tile counts
+# that the pieces do and do not divide, a last tile of one key, sink and window
+# inside pieces), runs over item boundaries, one query and one item
+@pytest.mark.parametrize("case", [
+    # n_q, N, w, s, H, d, dual
+    (256, 2048, 2048, 0, 4, 128, False), (300, 4673, 4673, 0, 6, 128, False), (300, 4673, 600, 65, 6, 128, True),
+    (1, 9001, 9001, 0, 1, 128, False), (70, 8000, 1000, 200, 2, 128, True), (520, 2500, 2500, 0, 20, 128, False),
+    (2400, 9361, 9361, 0, 14, 128, False),
+    (256, 2048, 2048, 0, 4, 64, False), (300, 4673, 1700, 65, 12, 64, True), (1, 9001, 9001, 0, 1, 64, False),
+    (1560, 6240, 6240, 0, 24, 64, False),
+])
+def test_automatic_split_parity(case):
+    n_q, N, w, s, H, d, dual = case
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    if n_cu == 256:
+        assert ispa.lib().ispa_attn_workspace_bytes(N, w, s, n_q, H, d, int(dual), 0) > 0
+    rows = sorted({0, n_q // 2, n_q - 1})
+    q, k, v = synth.chunk_qkv(16, 0, 0, n_q, N, H * d, DEV)
+    auto = ispa.attn_chunk(q, k, v, N, w, H, sink_len=s, dual=dual)
+    whole = ispa.attn_chunk(q, k, v, N, w, H, sink_len=s, dual=dual, segments=-1)
+    torch.cuda.synchronize()
+    ref = oracle.chunk_attention(f64(q), f64(k), f64(v), N, w, H, sink_len=s, query_rows=np.asarray(rows),
+                                 branches=("full", "local") if dual else ("local",))
+    for i, name in enumerate(("full", "local") if dual else ("local",)):
+        # both are within ATTN_TOL of the exact result, each with its own
+        # rounding of the softmax weights, so within twice that of each other
+        assert attn_err(f64(auto[2 * i]), f64(whole[2 * i])) <= 2 * ATTN_TOL, name + " split vs whole"
+        assert_lse(f64(auto[2 * i + 1]), f64(whole[2 * i + 1]), name + " lse split vs whole")
+        assert_attn(f64(auto[2 * i])[rows], ref[name][0], name)
+        assert_lse(f64(auto[2 * i + 1])[:, rows], ref[name][1], name + " lse")
+
+
+def test_split_calls_on_two_streams():
+    # split calls overlap on two streams: each has a workspace of its own
+    n_q, N, H, d = 256, 4096, 12, 128
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    sets = [synth.chunk_qkv(17, i, 0, n_q, N, H * d, DEV) for i in range(2)]
+    refs = [ispa.attn_chunk(*x, N, N, H) for x in sets]
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(8):
+        for st, x in zip(streams, sets):
+            with torch.cuda.stream(st):
+                got.append(ispa.attn_chunk(*x, N, N, H))
+    torch.cuda.synchronize()
+    for i, g in enumerate(got):
+        assert torch.equal(g[0], refs[i % 2][0]) and torch.equal(g[1], refs[i % 2][1])
 
 
 # the paper's literal decomposable form (Eq. 9-12): local and history branches
