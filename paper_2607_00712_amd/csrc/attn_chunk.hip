@@ -829,7 +829,7 @@ hipError_t launch_attn_chunk(const AttnArgs& a, int head_dim, hipStream_t stream
   if (attn_fast_eligible(a, head_dim)) {
     const bool fold = split_folds(a);  // the pieces complete their work items (counters cleared first)
     if (fold) {
-      e = launch_zero(a.split.ctr, (size_t)n_work * 2 * 4 * sizeof(uint32_t), stream);
+      e = launch_zero(a.split.ctr, (size_t)n_work * 2 * 4 * sizeof(uint32_t), nullptr, 0, stream);
       if (e != hipSuccess) return e;
     }
     e = launch_attn_fast(a, fold, stream);

@@ -321,8 +321,9 @@ int ispa_stats_reset(ispa_stats* h) {
   if (!valid_handle(h)) return ISPA_ERR_STATE;
   h->n_rows = 0;
   // G, C (contiguous at the start of the workspace) and the scalars
-  if (ispa::launch_zero(h->ws + h->lay.G, h->lay.L, h->stream) != hipSuccess) return ISPA_ERR_HIP;
-  if (ispa::launch_zero(h->ws + h->lay.scalars, 4 * sizeof(double), h->stream) != hipSuccess) return ISPA_ERR_HIP;
+  if (ispa::launch_zero(h->ws + h->lay.G, h->lay.L, h->ws + h->lay.scalars, 4 * sizeof(double), h->stream) !=
+      hipSuccess)
+    return ISPA_ERR_HIP;
   return ISPA_OK;
 }
 

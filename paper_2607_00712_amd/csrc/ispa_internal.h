@@ -109,7 +109,8 @@ int gram_tiles(int d_in, int d_out);
 hipError_t launch_gram(const uint16_t* x, const uint16_t* r, int64_t rows, int d_in, int d_out,
                        float* G, float* C, const double* sq_part, int n_sq_part, double* sq_norm,
                        float* scratch, size_t scratch_bytes, hipStream_t stream);
-hipError_t launch_zero(void* p, size_t bytes, hipStream_t stream);
+// zeroes bytes (a multiple of 16, p 16-byte aligned) at p and bytes2 (of 4) at p2
+hipError_t launch_zero(void* p, size_t bytes, void* p2, size_t bytes2, hipStream_t stream);
 // the hand-scheduled Gram kernel (gram_fast.cpp): widths that are multiples of
 // 256; tiles computed whole (n_whole) or as 2^log_pieces row pieces of `split`
 // stages (n_split tiles), the later pieces' sums in (2^log_pieces - 1) x n_split
