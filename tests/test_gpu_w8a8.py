@@ -51,6 +51,24 @@ def test_quantize_rows_bitwise(dtype, shape):
     assert np.array_equal(s.cpu().numpy().view(np.int32), want_s.view(np.int32))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("cols", [504, 512, 520, 1528, 1536, 1544, 5112, 5128, 6152])
+def test_quantize_rows_register_edges(dtype, cols):
+    # widths around the chunks of 512 and around the ones kept in registers, with
+    # quotients within a few ulp of a half, where the code hangs on the rounding
+    # of the quotient
+    g = torch.Generator().manual_seed(cols)
+    x = torch.randint(-126, 127, (21, cols), generator=g).float() + 0.5
+    x = x * (1 + torch.randint(-3, 4, (21, cols), generator=g) * 2.0 ** -23)
+    x[:, -1] = 127.0                      # the absmax, in the last column
+    x = (x * torch.exp(torch.empty((21, 1)).uniform_(-40.0, 40.0, generator=g))).to(dtype)
+    q, s = ispa.quantize_rows(x.to(DEV))
+    torch.cuda.synchronize()
+    want_q, want_s = oracle.quantize_rows(x.float().numpy())
+    assert np.array_equal(q.cpu().numpy(), want_q)
+    assert np.array_equal(s.cpu().numpy().view(np.int32), want_s.view(np.int32))
+
+
 def codes(rows, cols, g):
     return torch.randint(-127, 128, (rows, cols), generator=g, dtype=torch.int8)
 
