@@ -30,7 +30,7 @@
 //   of LDS traffic, updates and barriers.
 // Triangular solves in block LDL^T form over 256-blocks (details below): the
 //   inverses X_I of the 256 x 256 diagonal blocks of L and P_I = X_I^T X_I,
-//   Lh = L diag(X_I) below the 256-block diagonal, then one right-looking
+//   Lh = L diag(X_I) (stored transposed above the 256-block diagonal), then one right-looking
 //   rank-256 GEMM launch per block for the forward and for the backward sweep,
 //   with no diagonal work in them.
 // The panel updates and the sweeps run on the bf16 matrix cores with every fp32
@@ -388,7 +388,8 @@ __device__ __forceinline__ void tri_index(int t, int& ti, int& tj) {
 }
 
 // L = lower(G) + lambda I with zeros above the diagonal up to the end of the
-// row's 256-block (the part above the 256-block diagonal is never read),
+// row's 256-block (the part above the 256-block diagonal is never read before
+// Lh^T is written there),
 // status = 0. Row blockIdx.x, four columns per
 // thread (n is a multiple of 4); only G's lower triangle is read.
 __global__ void solve_init_kernel(const float* G, float* L, int n, float lambda, int* status, int64_t ws) {
@@ -712,10 +713,10 @@ __global__ __launch_bounds__(kThreads, 2) void chol_step_kernel(float* L, float*
 //   L^T dW = Z   <=>  Lh^T dW = V,  V_I = P_I Y_I
 // Both unit-triangular sweeps are right-looking rank-256 GEMM updates with no
 // diagonal work, one launch per block: Y_r -= Lh_rI Y_I (r > I) and
-// dW_I -= Lh_JI^T dW_J (I < J). Lh overwrites the strictly-below-256-block part
-// of L.
+// dW_I -= Lh_JI^T dW_J (I < J). Lh^T goes to the part of L above the 256-block
+// diagonal (so its product with L_rI need not run in place), which both sweeps
+// read: its rows as k in the forward sweep, as m in the backward one.
 constexpr int kBb = 256;  // block size of the triangular sweeps
-constexpr int kKc = 16;   // k rows per LDS chunk of the GEMM
 
 // quad() accumulated into acc
 template <bool TA, bool TB>
@@ -780,159 +781,55 @@ __global__ __launch_bounds__(kThreads) void inv256_kernel(const float* L, const 
   }
 }
 
-// C(m, n) = [C(m, n) -] sum_k A(m, k) B(k, n) for m < M, n < N, in fp32 MFMA.
-// B(k, n) = B[k * ldb + n]. A(m, k) = A[k * lda + m] (k-major), or
-// A[m * lda + k] for the m-major instantiation. One launch runs up to two jobs
-// that share B, N and K (tiles of job 0 first), batched over blockIdx.y with
-// element strides per batch and M growing by batch_dm per batch. Dimensions
-// are multiples of 4 and rows 16-byte aligned. Operands are staged through
-// LDS k-major (a row of 16 k-rows per chunk, double buffered) so that the
-// 32 lanes of an MFMA operand read 32 consecutive floats.
-struct GemmJob {
-  const float* A;
-  float* C;
-  int M;
-  int64_t lda, ldc;
-  int sub;                    // 1: C -= A B, 0: C = A B
-  int64_t la = 0, lc = 0;  // bytes per layer (blockIdx.z) of A and of C
-};
-struct GemmArgs {
-  GemmJob job[2];
-  int n_jobs;
-  const float* B;
-  int N, K;
-  int64_t ldb;
-  int64_t batch_a, batch_b, batch_c;
-  int batch_dm;
-  int64_t lb;  // bytes per layer (blockIdx.z) of B
-};
-
-template <int WM, int WN, int QM, int QN, bool A_MK>
-__global__ __launch_bounds__(kThreads) void gemm_kernel(GemmArgs g) {
-  constexpr int TM = WM * QM * 32, TN = WN * QN * 32;
-  constexpr int SA = TM + 32, SB = TN + 32;  // row strides: the two k rows of an operand read sit 32 banks apart
-  constexpr int kA4 = kKc * TM / 4;  // 16-byte pieces of an A chunk
-  constexpr int NA = (kA4 + kThreads - 1) / kThreads, NB = kKc * TN / 4 / kThreads;
-  static_assert(WM * WN == kThreads / 64 && NB >= 1 && kA4 % 64 == 0, "tile shape");
-  __shared__ __attribute__((aligned(16))) float As[2][kKc][SA];
-  __shared__ __attribute__((aligned(16))) float Bs[2][kKc][SB];
-
-  const int tiles_n = (g.N + TN - 1) / TN;
-  const int dm = (int)blockIdx.y * g.batch_dm;
-  const int m_tiles0 = (g.job[0].M + dm + TM - 1) / TM;
-  int t = blockIdx.x;
-  const bool second = t >= m_tiles0 * tiles_n;
-  if (second) {
-    if (g.n_jobs < 2) return;
-    t -= m_tiles0 * tiles_n;
-  }
-  const float* A = second ? g.job[1].A : g.job[0].A;
-  float* C = second ? g.job[1].C : g.job[0].C;
-  const int M = (second ? g.job[1].M : g.job[0].M) + dm;
-  const int64_t lda = second ? g.job[1].lda : g.job[0].lda;
-  const int64_t ldc = second ? g.job[1].ldc : g.job[0].ldc;
-  const int sub = second ? g.job[1].sub : g.job[0].sub;
-  const int m0 = (t / tiles_n) * TM, n0 = (t % tiles_n) * TN;
-  if (m0 >= M) return;
-  const int layer = blockIdx.z;
-  A = at_layer(A, second ? g.job[1].la : g.job[0].la, layer) + blockIdx.y * g.batch_a;
-  const float* B = at_layer(g.B, g.lb, layer) + blockIdx.y * g.batch_b;
-  C = at_layer(C, second ? g.job[1].lc : g.job[0].lc, layer) + blockIdx.y * g.batch_c;
-  const int N = g.N, K = g.K;
-
+// P_I = X_I^T X_I for 256-block I = blockIdx.y, 64 x 64 tile blockIdx.x of its lower
+// triangle, written with its mirror image. fp32 MFMA: a multiply-add chain rounded
+// to nearest, where the bf16 instruction cuts the products of a sum toward zero,
+// which leaves sums of squares low and would scale dW by 1.5e-7 (eps 3e-6 farther
+// from 64 bits). k starts at the tile's rows (X_I is lower triangular); 16 rows of
+// both operands per step, two LDS buffers. (Six blocks of 30 layers 29 us, 72 with
+// all tiles and all k; one layer 7.6 us, 14.6.)
+constexpr int kXk = 16;
+__global__ __launch_bounds__(kThreads) void xtx_kernel(const float* X, float* P, int d, int64_t ws) {
+  __shared__ __attribute__((aligned(16))) float As[2][kXk][kNb + 32], Bs[2][kXk][kNb + 32];
+  int ti, tj;
+  tri_index((int)blockIdx.x, ti, tj);
+  const int left = min(kBb, d - (int)blockIdx.y * kBb);
+  const int end = (left + kNb - 1) / kNb * kNb;  // X_I is zero past the matrix
+  if (ti * kNb >= end) return;
+  X = at_layer(X, ws, blockIdx.z) + (int64_t)blockIdx.y * kBb * kBb;
+  P = at_layer(P, ws, blockIdx.z) + (int64_t)blockIdx.y * kBb * kBb;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int h = lane >> 5, l32 = lane & 31;
-  const int wm0 = (wave / WN) * QM * 32, wn0 = (wave % WN) * QN * 32;
-
-  f32x4 ra[NA], rb[NB];
-  auto fetch_chunk = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < NA; ++q) {
-      const int e = threadIdx.x + q * kThreads;
-      if (e >= kA4) break;  // (wave-uniform: kA4 is a multiple of 64)
-      if (A_MK) {
-        const int m = e / (kKc / 4), k = (e % (kKc / 4)) * 4;
-        ra[q] = (m0 + m < M && k0 + k < K) ? *(const f32x4*)(A + (int64_t)(m0 + m) * lda + k0 + k)
-                                             : f32x4{0.f, 0.f, 0.f, 0.f};
-      } else {
-        const int k = e / (TM / 4), m = (e % (TM / 4)) * 4;
-        ra[q] = (k0 + k < K && m0 + m < M) ? *(const f32x4*)(A + (int64_t)(k0 + k) * lda + m0 + m)
-                                             : f32x4{0.f, 0.f, 0.f, 0.f};
-      }
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  const int k = threadIdx.x >> 4, c = (threadIdx.x & 15) * 4;
+  const float* xa = X + (int64_t)k * kBb + ti * kNb + c;
+  const float* xb = X + (int64_t)k * kBb + tj * kNb + c;
+  const int k0 = ti * kNb;
+  f32x4 ra = *(const f32x4*)(xa + (int64_t)k0 * kBb), rb = *(const f32x4*)(xb + (int64_t)k0 * kBb);
+  f32x16 acc = {};
+  int buf = 0;
+  for (int kk = k0; kk < end; kk += kXk, buf ^= 1) {
+    *(f32x4*)&As[buf][k][c] = ra;
+    *(f32x4*)&Bs[buf][k][c] = rb;
+    if (kk + kXk < end) {
+      ra = *(const f32x4*)(xa + (int64_t)(kk + kXk) * kBb);
+      rb = *(const f32x4*)(xb + (int64_t)(kk + kXk) * kBb);
     }
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      const int e = threadIdx.x + q * kThreads;
-      const int k = e / (TN / 4), nn = (e % (TN / 4)) * 4;
-      rb[q] = (k0 + k < K && n0 + nn < N) ? *(const f32x4*)(B + (int64_t)(k0 + k) * g.ldb + n0 + nn)
-                                            : f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-  };
-  auto put_chunk = [&](int buf) {
-#pragma unroll
-    for (int q = 0; q < NA; ++q) {
-      const int e = threadIdx.x + q * kThreads;
-      if (e >= kA4) break;
-      if (A_MK) {
-        const int m = e / (kKc / 4), k = (e % (kKc / 4)) * 4;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) As[buf][k + j][m] = ra[q][j];
-      } else {
-        const int k = e / (TM / 4), m = (e % (TM / 4)) * 4;
-        *(f32x4*)&As[buf][k][m] = ra[q];
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      const int e = threadIdx.x + q * kThreads;
-      const int k = e / (TN / 4), nn = (e % (TN / 4)) * 4;
-      *(f32x4*)&Bs[buf][k][nn] = rb[q];
-    }
-  };
-
-  f32x16 acc[QM][QN];
-#pragma unroll
-  for (int i = 0; i < QM; ++i)
-#pragma unroll
-    for (int j = 0; j < QN; ++j) acc[i][j] = f32x16{};
-
-  const int nk = (K + kKc - 1) / kKc;
-  fetch_chunk(0);
-  put_chunk(0);
-  __syncthreads();
-  for (int c = 0; c < nk; ++c) {
-    const int buf = c & 1;
-    if (c + 1 < nk) fetch_chunk((c + 1) * kKc);
-#pragma unroll
-    for (int kk = 0; kk < kKc; kk += 2) {
-      float a[QM], b[QN];
-#pragma unroll
-      for (int i = 0; i < QM; ++i) a[i] = As[buf][kk + h][wm0 + 32 * i + l32];
-#pragma unroll
-      for (int j = 0; j < QN; ++j) b[j] = Bs[buf][kk + h][wn0 + 32 * j + l32];
-#pragma unroll
-      for (int i = 0; i < QM; ++i)
-#pragma unroll
-        for (int j = 0; j < QN; ++j) acc[i][j] = mfma_f32(a[i], b[j], acc[i][j]);
-    }
-    if (c + 1 < nk) put_chunk(buf ^ 1);
+    // one barrier per step: a wave that writes this buffer again has passed the next
+    // step's barrier, which every wave reaches after reading this one
     __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kXk; j += 2) acc = mfma_f32(As[buf][j + h][wm + l32], Bs[buf][j + h][wn + l32], acc);
   }
-
+  const int col = tj * kNb + wn + l32;
 #pragma unroll
-  for (int i = 0; i < QM; ++i)
+  for (int r = 0; r < 16; r += 4) {
+    const int row = ti * kNb + wm + acc_row(r, lane);
+    const f32x4 v = {acc[r], acc[r + 1], acc[r + 2], acc[r + 3]};
 #pragma unroll
-    for (int j = 0; j < QN; ++j) {
-      const int col = n0 + wn0 + 32 * j + l32;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = m0 + wm0 + 32 * i + acc_row(r, lane);
-        if (row < M && col < N) {
-          float* p = C + (int64_t)row * ldc + col;
-          *p = sub ? *p - acc[i][j][r] : acc[i][j][r];
-        }
-      }
-    }
+    for (int e = 0; e < 4; ++e) P[(int64_t)(row + e) * kBb + col] = v[e];
+    if (ti != tj) *(f32x4*)&P[(int64_t)col * kBb + row] = v;
+  }
 }
 
 // <dW, C> and ||dW||^2 in two passes: each of kEpsBlocks workgroups reduces a
@@ -1030,8 +927,8 @@ namespace {
 // ahead into registers and cut and written to LDS one stage ahead (two buffers,
 // one barrier per stage): the cut is done once per workgroup, not per wave, and
 // three planes of rows with k contiguous make an operand one ds_read_b128 per
-// plane. B(k, n) = B[k ldb + n]; A(m, k) = A[m lda + k] (A_KM = false) or A[k lda
-// + m] (true), so the lower triangle of L serves both sweeps. The minuend's
+// plane. A(m, k) = A[m lda + k] (A_KM = false) or A[k lda + m] (true), B likewise,
+// so one copy of Lh serves both sweeps. The minuend's
 // loads are issued before the last stage's products (30 layers of 1536: the
 // first forward launch 275 us against 377 with the loads at the end, 395 with
 // the fp32 kernel before). What bounds it: 0.75 of the time of a launch is loads,
@@ -1056,6 +953,11 @@ struct SplitArgs {
   SplitJob job[2];
   int n_jobs, N, layers;
   int64_t ldb, lb;  // lb: bytes per layer of B
+  int tri = 0;     // A(m, k) is zero for k < m: skipped
+  // one job over `batch` diagonal blocks: A, B and C advance by these elements per
+  // block, and N is capped to what is left of the rows, N_left - kBb per block
+  int batch = 1, N_left = 1 << 30;
+  int64_t ba = 0, bb = 0, bc = 0;
 };
 
 // One side of the tile: T rows of the LDS planes (the m or n index), KS k; every
@@ -1123,30 +1025,43 @@ struct SplitSide {
   }
 };
 
-template <int Q, bool A_KM>
+template <int Q, bool A_KM, bool B_KM>
 __global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(SplitArgs g) {
   constexpr int T = 64 * Q;
   using SideA = SplitSide<T, A_KM>;
-  using SideB = SplitSide<T, true>;
+  using SideB = SplitSide<T, B_KM>;
   constexpr int kKs = SideA::kKs, kSide = SideA::kBytes;
   __shared__ __attribute__((aligned(1024))) char smem[2][2 * kSide];
-  // consecutive tiles (n fastest, then m, job, layer) on one XCD
-  const int tiles_n = (g.N + T - 1) / T;
-  const int t0 = (g.job[0].M + T - 1) / T * tiles_n;
-  const int t1 = g.n_jobs > 1 ? (g.job[1].M + T - 1) / T * tiles_n : 0;
-  const int total = (t0 + t1) * g.layers;
+  // consecutive tiles (n fastest, then m, job or block, layer) on one XCD
   const int idx = (int)(blockIdx.x & 7) * ((int)gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-  if (idx >= total) return;
-  const int layer = idx / (t0 + t1);
-  int t = idx - layer * (t0 + t1);
-  const SplitJob& jb = t < t0 ? g.job[0] : g.job[1];
-  if (t >= t0) t -= t0;
+  auto tiles = [](int n) { return n > 0 ? (n + T - 1) / T : 0; };
+  int per_layer = 0;
+  for (int i = 0; i < g.batch; ++i)
+    per_layer += tiles(g.job[0].M) * tiles(min(g.N, g.N_left - i * kBb));
+  if (g.n_jobs > 1) per_layer += tiles(g.job[1].M) * tiles(g.N);
+  if (idx >= per_layer * g.layers) return;
+  const int layer = idx / per_layer;
+  int t = idx - layer * per_layer, blk = 0;
+  bool second = false;
+  for (;;) {  // ends: t is below the sum of these counts
+    const int n = tiles(g.job[0].M) * tiles(min(g.N, g.N_left - blk * kBb));
+    if (t < n) break;
+    t -= n;
+    if (++blk == g.batch) {
+      second = true;
+      blk = 0;
+      break;
+    }
+  }
+  const SplitJob& jb = second ? g.job[1] : g.job[0];
+  const int M = jb.M, K = jb.K;
+  const int N = second ? g.N : min(g.N, g.N_left - blk * kBb);
+  const int tiles_n = tiles(N);
   const int m0 = t / tiles_n * T, n0 = t % tiles_n * T;
-  const int M = jb.M, N = g.N, K = jb.K;
   SideA sa;
   SideB sb;
-  sa.init(at_layer(jb.A, jb.la, layer), jb.lda, m0, M, K);
-  sb.init(at_layer(jb.B, g.lb, layer), g.ldb, n0, N, K);
+  sa.init(at_layer(jb.A, jb.la, layer) + blk * g.ba, jb.lda, m0, M, K);
+  sb.init(at_layer(jb.B, g.lb, layer) + blk * g.bb, g.ldb, n0, N, K);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l32 = lane & 31, h = lane >> 5;
@@ -1158,8 +1073,8 @@ __global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(Sp
 #pragma unroll
     for (int j = 0; j < Q; ++j) acc[i][j] = f32x16{};
 
-  float* C = at_layer(jb.C, jb.lc, layer);
-  const float* Cin = at_layer(jb.Cin, jb.lc, layer);
+  float* C = at_layer(jb.C, jb.lc, layer) + blk * g.bc;
+  const float* Cin = at_layer(jb.Cin, jb.lc, layer);  // never with several blocks
 
   // the minuend and the result: rows past M read zero and are not stored
   float cin[Q][Q][16];
@@ -1174,18 +1089,25 @@ __global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(Sp
   }
 
   const int steps = (K + kKs - 1) / kKs;
-  sa.load(0);
-  sb.load(0);
-  if (kKs > K) sa.mask(0, K);
+  const int s0 = g.tri ? m0 / kKs : 0;  // the first stage that is not all zero
+  auto mask = [&](int s) {
+    if ((s + 1) * kKs > K) {
+      sa.mask(s * kKs, K);
+      sb.mask(s * kKs, K);
+    }
+  };
+  sa.load(s0);
+  sb.load(s0);
+  mask(s0);
   sa.put(smem[0]);
   sb.put(smem[0] + kSide);
-  if (steps > 1) {
-    sa.load(1);
-    sb.load(1);
+  if (s0 + 1 < steps) {
+    sa.load(s0 + 1);
+    sb.load(s0 + 1);
   }
   __syncthreads();
-  for (int s = 0; s < steps; ++s) {
-    const char* la = smem[s & 1];
+  for (int s = s0; s < steps; ++s) {
+    const char* la = smem[(s - s0) & 1];
     const char* lb = la + kSide;
     if (s == steps - 1) {  // the minuend's loads pass under the last stage's products
 #pragma unroll
@@ -1220,9 +1142,10 @@ __global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(Sp
     }
     // the other buffer was read in stage s - 1, before the last barrier
     if (s + 1 < steps) {
-      if ((s + 2) * kKs > K) sa.mask((s + 1) * kKs, K);
-      sa.put(smem[(s + 1) & 1]);
-      sb.put(smem[(s + 1) & 1] + kSide);
+      mask(s + 1);
+      char* const next = smem[(s - s0 + 1) & 1];
+      sa.put(next);
+      sb.put(next + kSide);
       if (s + 2 < steps) {
         sa.load(s + 2);
         sb.load(s + 2);
@@ -1260,19 +1183,23 @@ namespace {
 // 4.15 against 4.41 ms) but leave the chip idle with fewer (one layer of 1536:
 // 0.79 ms against 0.64).
 constexpr int kSplitBigTiles = 256;
-template <bool A_KM>
+template <bool A_KM, bool B_KM = true>
 hipError_t launch_split(const SplitArgs& g, hipStream_t stream) {
   auto tiles = [&](int T) {
+    auto up = [&](int n) -> int64_t { return n > 0 ? (n + T - 1) / T : 0; };
     int64_t n = 0;
-    for (int j = 0; j < g.n_jobs; ++j) n += (int64_t)((g.job[j].M + T - 1) / T) * ((g.N + T - 1) / T);
+    for (int i = 0; i < g.batch; ++i)
+      n += up(g.job[0].M) * up(min(g.N, g.N_left - i * kBb));
+    if (g.n_jobs > 1) n += up(g.job[1].M) * up(g.N);
     return n * g.layers;
   };
   const bool big = tiles(128) >= kSplitBigTiles;
   const int grid = (int)((tiles(big ? 128 : 64) + 7) / 8 * 8);
+  if (grid == 0) return hipSuccess;
   if (big) {
-    hipLaunchKernelGGL((gemm_split_kernel<2, A_KM>), dim3(grid), dim3(kThreads), 0, stream, g);
+    hipLaunchKernelGGL((gemm_split_kernel<2, A_KM, B_KM>), dim3(grid), dim3(kThreads), 0, stream, g);
   } else {
-    hipLaunchKernelGGL((gemm_split_kernel<1, A_KM>), dim3(grid), dim3(kThreads), 0, stream, g);
+    hipLaunchKernelGGL((gemm_split_kernel<1, A_KM, B_KM>), dim3(grid), dim3(kThreads), 0, stream, g);
   }
   return hipGetLastError();
 }
@@ -1505,39 +1432,25 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
                          apply, w.status, ws, none);
     }
   }
-  // X_I, P_I = X_I^T X_I, Lh below the 256-block diagonal
+  // the inverses X_I of the diagonal blocks, P_I = X_I^T X_I, and Lh_rI = L_rI X_I
+  // for the rows below, stored transposed above the diagonal blocks
   hipLaunchKernelGGL(inv256_kernel, dim3(nb, 4, nl), dim3(kThreads), 0, stream, L, w.dinv, xinv, d, ws);
-  {
-    GemmArgs g = {};
-    g.job[0] = GemmJob{xinv, pinv, kBb, kBb, kBb, 0};
-    g.job[0].la = g.job[0].lc = ws;
-    g.lb = ws;
-    g.n_jobs = 1;
-    g.B = xinv;
-    g.N = kBb;
-    g.K = kBb;
-    g.ldb = kBb;
-    g.batch_a = g.batch_b = g.batch_c = (int64_t)kBb * kBb;
-    hipLaunchKernelGGL((gemm_kernel<2, 2, 1, 1, false>), dim3(16, nb, nl), dim3(kThreads), 0, stream, g);
-  }
+  hipLaunchKernelGGL(xtx_kernel, dim3(10, nb, nl), dim3(kThreads), 0, stream, xinv, pinv, d, ws);
   if (nb > 1) {
-    // Lh_rI = L_rI X_I in place: a workgroup owns 32 rows x the whole 256-block
-    // (all of its A is read before any of its C is written)
-    GemmArgs g = {};
-    float* first = L + (int64_t)kBb * d;  // rows of block 1, columns of block 0
-    g.job[0] = GemmJob{first, first, d - kBb, d, d, 0};
-    g.job[0].la = g.job[0].lc = ws;
-    g.lb = ws;
+    // (m, n) = (column of block I, row below it), for every block that has rows below
+    SplitArgs g = {};
+    g.job[0] = SplitJob{xinv, L + kBb, nullptr, L + (int64_t)kBb * d, kBb, kBb, kBb, d, ws, ws};
     g.n_jobs = 1;
-    g.B = xinv;
-    g.N = kBb;
-    g.K = kBb;
-    g.ldb = kBb;
-    g.batch_a = g.batch_c = (int64_t)kBb * d + kBb;
-    g.batch_b = (int64_t)kBb * kBb;
-    g.batch_dm = -kBb;
-    hipLaunchKernelGGL((gemm_kernel<1, 4, 1, 2, true>), dim3((d - kBb + 31) / 32, nb - 1, nl), dim3(kThreads), 0,
-                       stream, g);
+    g.N = g.N_left = d - kBb;
+    g.layers = nl;
+    g.ldb = d;
+    g.lb = ws;
+    g.tri = 1;
+    g.batch = nb - 1;
+    g.ba = (int64_t)kBb * kBb;
+    g.bb = g.bc = (int64_t)kBb * d + kBb;
+    const hipError_t e = launch_split<true, false>(g, stream);
+    if (e != hipSuccess) return e;
   }
   // The sweeps treat each column of the right-hand side on its own, so from
   // d = 4096 on the columns go in two halves, each on a stream of its own (the
@@ -1548,14 +1461,15 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
   // 0.97, 1536 0.66 -> 0.69 ms (halves too small to fill the chip).
   auto yblk = [&](auto* base, int I) { return base + (int64_t)I * kBb * d_out; };
   auto kblk = [&](int I) { return min(kBb, d - I * kBb); };
-  auto low = [&](int r, int I) { return L + (int64_t)r * kBb * d + (int64_t)I * kBb; };  // rows of block r, columns of I
+  // Lh transposed: rows of block I, columns of block r > I
+  auto up = [&](int I, int r) { return L + (int64_t)I * kBb * d + (int64_t)r * kBb; };
   auto sweeps = [&](int col0, int ncols, hipStream_t st) -> hipError_t {
     // forward sweep: Y_r -= Lh_rI Y_I (r > I) and dW_I = P_I Y_I. After the first
     // block the blocks go in pairs (I, I+1): one launch finishes Y_{I+1} and forms
     // dW_I, the next updates every later block with both (depth 512, so the
     // read-modify-write of the right-hand side below is shared by two blocks)
-    // and forms dW_{I+1}. The A operand is the rows of Lh below, whose columns of
-    // blocks I and I+1 are consecutive. Row pointers of
+    // and forms dW_{I+1}. The A operand is Lh transposed, whose rows of blocks I
+    // and I+1 are consecutive. Row pointers of
     // the right-hand side, Y and dW are taken at column 0 and moved to col0 here.
     auto fwd_launch = [&](const float* A, float* Ydst, const float* Ysrc, int M, const float* Bsum, int Ksum,
                           int P, const float* Bp, int Kp) -> hipError_t {
@@ -1569,11 +1483,11 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
       g.layers = nl;
       g.ldb = d_out;
       g.lb = ws;
-      return launch_split<false>(g, st);
+      return launch_split<true>(g, st);
     };
     hipError_t e;
     // the first step reads the right-hand side C itself (Y = C before any update)
-    e = fwd_launch(low(1, 0), yblk(Y, 1), yblk(C, 1), d - kBb, C, kblk(0), 0, C, kblk(0));
+    e = fwd_launch(up(0, 1), yblk(Y, 1), yblk(C, 1), d - kBb, C, kblk(0), 0, C, kblk(0));
     if (e != hipSuccess) return e;
     for (int I = 1; I < nb; I += 2) {
       if (I + 1 == nb) {
@@ -1581,11 +1495,11 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
         if (e != hipSuccess) return e;
         break;
       }
-      e = fwd_launch(low(I + 1, I), yblk(Y, I + 1), yblk(Y, I + 1), kblk(I + 1), yblk(Y, I), kBb, I, yblk(Y, I),
+      e = fwd_launch(up(I, I + 1), yblk(Y, I + 1), yblk(Y, I + 1), kblk(I + 1), yblk(Y, I), kBb, I, yblk(Y, I),
                      kBb);
       if (e != hipSuccess) return e;
       const int below = d - (I + 2) * kBb;
-      e = fwd_launch(below > 0 ? low(I + 2, I) : nullptr, below > 0 ? yblk(Y, I + 2) : Y,
+      e = fwd_launch(below > 0 ? up(I, I + 2) : nullptr, below > 0 ? yblk(Y, I + 2) : Y,
                      below > 0 ? yblk(Y, I + 2) : Y, max(below, 0), yblk(Y, I), kBb + kblk(I + 1), I + 1,
                      yblk(Y, I + 1), kblk(I + 1));
       if (e != hipSuccess) return e;
@@ -1596,13 +1510,13 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
     auto bwd_launch = [&](int J, int M, int K, int row0) -> hipError_t {
       SplitArgs g = {};
       float* dst = delta_w + (int64_t)row0 * d_out + col0;
-      g.job[0] = SplitJob{L + (int64_t)J * kBb * d + row0, dst, dst, yblk(delta_w, J) + col0, M, K, d, d_out, ws, dws};
+      g.job[0] = SplitJob{L + (int64_t)row0 * d + (int64_t)J * kBb, dst, dst, yblk(delta_w, J) + col0, M, K, d, d_out, ws, dws};
       g.n_jobs = 1;
       g.N = ncols;
       g.layers = nl;
       g.ldb = d_out;
       g.lb = dws;
-      return launch_split<true>(g, st);
+      return launch_split<false>(g, st);
     };
     for (int J = nb - 1; J >= 1; J -= 2) {
       e = bwd_launch(J, kBb, kblk(J), (J - 1) * kBb);
