@@ -931,7 +931,9 @@ namespace {
 // so one copy of Lh serves both sweeps. The minuend's
 // loads are issued before the last stage's products (30 layers of 1536: the
 // first forward launch 275 us against 377 with the loads at the end, 395 with
-// the fp32 kernel before). What bounds it: 0.75 of the time of a launch is loads,
+// the fp32 kernel before). The stages run as straight code up to the last two,
+// which lets the compiler place the cuts among the products (the batch 2.54 ->
+// 2.43 ms; forcing an order of the instructions was 1-5% slower). What bounds it: 0.75 of the time of a launch is loads,
 // cuts and barriers that two workgroups per CU do not hide (132 TFLOP/s there,
 // 145 at one layer of 5120, against 92-110 before).
 //
@@ -1106,18 +1108,8 @@ __global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(Sp
     sb.load(s0 + 1);
   }
   __syncthreads();
-  for (int s = s0; s < steps; ++s) {
-    const char* la = smem[(s - s0) & 1];
-    const char* lb = la + kSide;
-    if (s == steps - 1) {  // the minuend's loads pass under the last stage's products
-#pragma unroll
-      for (int i = 0; i < Q; ++i)
-#pragma unroll
-        for (int j = 0; j < Q; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            cin[i][j][r] = ld1(rc, cof[j], (32 * i + acc_row(r, 0)) * ldc4);
-    }
+  auto products = [&](const char* la) {
+    const char* const lb = la + kSide;
 #pragma unroll
     for (int kk = 0; kk < kKs / 16; ++kk) {
       bf16x8 a[Q][3], b[Q][3];
@@ -1140,6 +1132,32 @@ __global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(Sp
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][pa[pr]], b[j][pb[pr]], acc[i][j], 0, 0, 0);
       }
     }
+  };
+  int s = s0;
+  // stages whose next one is whole, in one piece of straight code: the next
+  // stage's cuts between this one's matrix instructions (stages past the end
+  // load zeros or unused neighbours)
+  for (; (s + 2) * kKs <= K; ++s) {
+    products(smem[(s - s0) & 1]);
+    char* const next = smem[(s - s0 + 1) & 1];
+    sa.put(next);
+    sb.put(next + kSide);
+    sa.load(s + 2);
+    sb.load(s + 2);
+    __syncthreads();
+  }
+  for (; s < steps; ++s) {
+    const char* la = smem[(s - s0) & 1];
+    if (s == steps - 1) {  // the minuend's loads pass under the last stage's products
+#pragma unroll
+      for (int i = 0; i < Q; ++i)
+#pragma unroll
+        for (int j = 0; j < Q; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            cin[i][j][r] = ld1(rc, cof[j], (32 * i + acc_row(r, 0)) * ldc4);
+    }
+    products(la);
     // the other buffer was read in stage s - 1, before the last barrier
     if (s + 1 < steps) {
       mask(s + 1);
