@@ -153,7 +153,7 @@ hipError_t launch_quantize_rows(const void* x, int x_bf16, int64_t rows, int col
 
 // ---- solve (solve.hip) ----
 struct SolveWork {
-  float* L;          // [d, d] factor (lower triangle)
+  float* L;          // [d, d] factor (lower triangle), then Lh transposed above the 256-block diagonal
   float* work;       // [d, d_out] right-hand side being reduced
   float* dinv;       // [ceil(d/64), 64, 64] inverses of the diagonal blocks of L
   int* status;       // device int: 0 ok, 1 not SPD

@@ -1196,10 +1196,12 @@ namespace {
 
 // Launches a split GEMM of up to two jobs for every layer: 128 x 128 tiles when
 // there is at least one for each compute unit, else 64 x 64. 128 x 128 tiles
-// halve the cutting and the operand reads per product (30 layers of 1536: the
-// whole batch 3.32 ms against 3.61 with 64 x 64 throughout; one layer of 5120
-// 4.15 against 4.41 ms) but leave the chip idle with fewer (one layer of 1536:
-// 0.79 ms against 0.64).
+// halve the cutting and the operand reads per product (whole solves, 64 x 64
+// throughout -> this rule: 30 layers of 1536 2.69 -> 2.43 ms, one of 5120 3.35 ->
+// 3.12, 4096 2.00 -> 1.90, 3072 1.19 -> 1.17) but leave the chip idle with
+// fewer (128 x 128 throughout: one layer of 1536 0.57 ms against 0.45, 2048 0.78
+// against 0.63, four layers of 1536 0.72 against 0.67, one of 5120 3.21 against
+// 3.12).
 constexpr int kSplitBigTiles = 256;
 template <bool A_KM, bool B_KM = true>
 hipError_t launch_split(const SplitArgs& g, hipStream_t stream) {
@@ -1474,9 +1476,9 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
   // d = 4096 on the columns go in two halves, each on a stream of its own (the
   // caller's and a second one), whose launches fill each other's last rounds
   // of tiles and hide each other's short launches; every element's arithmetic
-  // is unchanged. Measured (one solve, alternating, medians of 10): d = 5120
-  // 4.75 -> 4.59 ms; d = 3072 1.70 -> 1.72, 2560 1.30 -> 1.34, 2048 0.91 ->
-  // 0.97, 1536 0.66 -> 0.69 ms (halves too small to fill the chip).
+  // is unchanged. Measured (one solve, alternating, medians of 5): d = 5120
+  // 3.25 -> 3.11 ms, 4096 1.97 -> 1.89; d = 3072 1.17 -> 1.20, 2048 0.63 ->
+  // 0.66, 1536 0.45 -> 0.49 ms (halves too small to fill the chip).
   auto yblk = [&](auto* base, int I) { return base + (int64_t)I * kBb * d_out; };
   auto kblk = [&](int I) { return min(kBb, d - I * kBb); };
   // Lh transposed: rows of block I, columns of block r > I
