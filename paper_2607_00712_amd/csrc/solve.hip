@@ -54,9 +54,6 @@ namespace {
 constexpr int kNb = 64;
 constexpr int kSup = 4;  // panels per super-panel of the deferred trailing update
 constexpr int kThreads = 256;
-constexpr int kLd = 65;  // LDS row stride (floats) of a 64 x 64 tile
-
-typedef float Tile[kNb][kLd];
 
 // Batched solves (one per layer, the layer from the last grid dimension): the
 // layers' workspaces are `bytes` apart.
@@ -69,65 +66,8 @@ __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-// acc(32x32) += op(A)[a0 + i, k] . op(B)[k, b0 + j] over k = 0..K-1 for one wave.
-// Non-transposed: A_op(i, k) = A[a0 + i][ak + k], B_op(k, j) = B[bk + k][b0 + j].
-// TA: A_op(i, k) = A[ak + k][a0 + i].  TB: B_op(k, j) = B[b0 + j][bk + k].
-template <bool TA, bool TB>
-__device__ __forceinline__ void mma(f32x16& acc, const float (*A)[kLd], int a0, int ak, const float (*B)[kLd],
-                                    int b0, int bk, int K, int lane) {
-  const int i = lane & 31, kh = lane >> 5;
-  for (int k = 0; k < K; k += 2) {
-    const float a = TA ? A[ak + k + kh][a0 + i] : A[a0 + i][ak + k + kh];
-    const float b = TB ? B[b0 + i][bk + k + kh] : B[bk + k + kh][b0 + i];
-    acc = mfma_f32(a, b, acc);
-  }
-}
-
 // accumulator element r of lane l sits at (row, col) of the 32 x 32 quadrant
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
-
-// A 64 x 64 block of a row-major matrix (ld) in flight: four 16-byte pieces per
-// thread. Rows >= rows_ok or cols >= cols_ok read as zero (ragged last block).
-// Row starts are 16-byte aligned and cols_ok is a multiple of 4 (dimensions are
-// multiples of 8). fetch() issues the global loads, put() writes LDS, so the
-// loads of several tiles can be in flight together.
-struct Frag {
-  f32x4 v[4];
-};
-__device__ __forceinline__ void fetch(Frag& f, const float* src, int64_t ld, int rows_ok, int cols_ok) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = threadIdx.x + q * kThreads;
-    const int r = e >> 4, c = (e & 15) * 4;
-    f.v[q] = (r < rows_ok && c < cols_ok) ? *(const f32x4*)(src + (int64_t)r * ld + c) : f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-}
-__device__ __forceinline__ void put(Tile& t, const Frag& f) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = threadIdx.x + q * kThreads;
-    const int r = e >> 4, c = (e & 15) * 4;
-    t[r][c + 0] = f.v[q][0];
-    t[r][c + 1] = f.v[q][1];
-    t[r][c + 2] = f.v[q][2];
-    t[r][c + 3] = f.v[q][3];
-  }
-}
-__device__ __forceinline__ void load_tile(Tile& t, const float* src, int64_t ld, int rows_ok, int cols_ok) {
-  Frag f;
-  fetch(f, src, ld, rows_ok, cols_ok);
-  put(t, f);
-}
-__device__ __forceinline__ void store_tile(const Tile& t, float* dst, int64_t ld, int rows_ok, int cols_ok) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = threadIdx.x + q * kThreads;
-    const int r = e >> 4, c = (e & 15) * 4;
-    if (r < rows_ok && c < cols_ok) {
-      *(f32x4*)(dst + (int64_t)r * ld + c) = f32x4{t[r][c], t[r][c + 1], t[r][c + 2], t[r][c + 3]};
-    }
-  }
-}
 
 typedef unsigned int u32;
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -359,25 +299,6 @@ __device__ __forceinline__ void mma6(f32x16& acc, const bf16x8 (&a)[3], const bf
   constexpr int pa[6] = {2, 1, 0, 1, 0, 0}, pb[6] = {0, 1, 2, 0, 1, 0};
 #pragma unroll
   for (int p = 0; p < 6; ++p) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pa[p]], b[pb[p]], acc, 0, 0, 0);
-}
-
-// Quadrant product over a full 64-deep tile pair, one quadrant per wave:
-// acc = op(A)[wr.., :] op(B)[:, wc..]
-template <bool TA, bool TB>
-__device__ __forceinline__ f32x16 quad(const Tile& A, const Tile& B) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  f32x16 acc = {};
-  mma<TA, TB>(acc, A, (wave >> 1) * 32, 0, B, (wave & 1) * 32, 0, kNb, lane);
-  return acc;
-}
-__device__ __forceinline__ void quad_store(Tile& D, const f32x16& acc, float sign, bool add) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r0 = (wave >> 1) * 32, c0 = (wave & 1) * 32;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    float& d = D[r0 + acc_row(r, lane)][c0 + (lane & 31)];
-    d = add ? d + sign * acc[r] : sign * acc[r];
-  }
 }
 
 __device__ __forceinline__ void tri_index(int t, int& ti, int& tj) {
@@ -718,66 +639,114 @@ __global__ __launch_bounds__(kThreads, 2) void chol_step_kernel(float* L, float*
 // read: its rows as k in the forward sweep, as m in the backward one.
 constexpr int kBb = 256;  // block size of the triangular sweeps
 
-// quad() accumulated into acc
-template <bool TA, bool TB>
-__device__ __forceinline__ void quad_acc(f32x16& acc, const Tile& A, const Tile& B) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  mma<TA, TB>(acc, A, (wave >> 1) * 32, 0, B, (wave & 1) * 32, 0, kNb, lane);
-}
-__device__ __forceinline__ void quad_put(Tile& D, const f32x16& acc, float sign) {
-  quad_store(D, acc, sign, false);
-}
-
-// X_I = L_II^-1 for 256-block I = blockIdx.x, 64-column strip b = blockIdx.y:
-// X_bb = Dinv_b and, for a > b, X_ab = -Dinv_a sum_{c=b}^{a-1} L_ac X_cb (64-block
-// indices inside the 256-block). Writes the full 256 x 64 strip of X_I (zeros
-// above the diagonal and in 64-blocks past the end of the matrix).
+// X_I = L_II^-1 for 256-block I = blockIdx.x, 32-column strip blockIdx.y (in 64-block
+// column b): X_bb = Dinv_b and, for a > b, X_ab = -Dinv_a sum_{c=b}^{a-1} L_ac X_cb
+// (64-block indices inside the 256-block). Writes the full 256 x 32 strip of X_I
+// (zeros above the diagonal and in 64-blocks past the end of the matrix).
+// A chain of up to nine 64 x 64 x 32 products, bound by their latency and the fp32
+// MFMAs (16 dependent steps of 16x16x4 each): 32-column strips for twice the
+// workgroups of 64, the next factor tile loading into registers (as a buffer, no
+// branch around a load) during each product. One layer of 1536
+// 12.9 us, 30 layers 36.0 (64-column strips, each tile loaded when it is due: 21.4
+// and 61.9).
+constexpr int kXw = 32;   // columns of a strip
+constexpr int kXld = 33;  // LDS row stride of its blocks
 __global__ __launch_bounds__(kThreads) void inv256_kernel(const float* L, const float* Dinv, float* Xinv, int n,
                                                          int64_t ws) {
-  __shared__ Tile Xc[4];
-  __shared__ Tile U;
+  __shared__ __attribute__((aligned(16))) RowTile U;
+  __shared__ float Xc[4][kNb][kXld];
   L = at_layer(L, ws, blockIdx.z);
   Dinv = at_layer(Dinv, ws, blockIdx.z);
   Xinv = at_layer(Xinv, ws, blockIdx.z);
   const int nblk = (n + kNb - 1) / kNb;
-  const int I = blockIdx.x, b = blockIdx.y;
-  const int g0 = I * 4;                       // first 64-block of the 256-block
-  const int n64 = min(4, nblk - g0);          // 64-blocks inside the matrix
-  float* X = Xinv + (int64_t)I * kBb * kBb;  // [256][256], row-major
-  if (b < n64) {
-    load_tile(Xc[b], Dinv + (int64_t)(g0 + b) * kNb * kNb, kNb, kNb, kNb);
-    __syncthreads();
-    for (int a = b + 1; a < n64; ++a) {
-      const int ra = min(kNb, n - (g0 + a) * kNb);
-      f32x16 t = {};
-      for (int c = b; c < a; ++c) {
-        load_tile(U, L + (int64_t)(g0 + a) * kNb * n + (int64_t)(g0 + c) * kNb, n, ra, kNb);
-        __syncthreads();
-        quad_acc<false, false>(t, U, Xc[c]);
-        __syncthreads();
-      }
-      // Xc[a] = -Dinv_a . T: T goes through Xc[a], Dinv_a through U
-      quad_put(Xc[a], t, 1.f);
-      load_tile(U, Dinv + (int64_t)(g0 + a) * kNb * kNb, kNb, kNb, kNb);
-      __syncthreads();
-      const f32x16 x = quad<false, false>(U, Xc[a]);
-      __syncthreads();
-      quad_put(Xc[a], x, -1.f);
-      __syncthreads();
+  const int I = blockIdx.x, b = blockIdx.y >> 1, half = blockIdx.y & 1;
+  const int g0 = I * 4;                 // first 64-block of the 256-block
+  const int n64 = min(4, nblk - g0);    // 64-blocks inside the matrix
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  const int g = lane >> 4, l16 = lane & 15;
+  const int tr = threadIdx.x >> 4, tc = (threadIdx.x & 15) * 4;  // a thread's piece of a 64 x 64 tile: rows tr + 16 q
+  float* X = Xinv + (int64_t)I * kBb * kBb + b * kNb + half * kXw;  // the strip, rows of 256
+  for (int a = 0; a < 4; ++a) {
+    if (b < n64 && a >= b && a < n64) continue;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int e = threadIdx.x + q * kThreads;
+      *(f32x4*)(X + (int64_t)(a * kNb + (e >> 3)) * kBb + (e & 7) * 4) = f32x4{0.f, 0.f, 0.f, 0.f};
     }
   }
-  for (int a = 0; a < 4; ++a) {
-    float* dst = X + (int64_t)a * kNb * kBb + b * kNb;
-    if (b < n64 && a >= b && a < n64) {
-      store_tile(Xc[a], dst, kBb, kNb, kNb);
-    } else {
+  if (b >= n64) return;
+
+  f32x4 u[4];
+  // tile (a, c) of the chain: L_ac, or Dinv_a for c = a
+  auto issue = [&](int a, int c) {
+    const bool dia = c == a;
+    const float* src = dia ? Dinv + (int64_t)(g0 + a) * kNb * kNb
+                           : L + (int64_t)(g0 + a) * kNb * n + (int64_t)(g0 + c) * kNb;
+    const int ld = dia ? kNb : n, rows = dia ? kNb : min(kNb, n - (g0 + a) * kNb);
+    const __amdgpu_buffer_rsrc_t rs = rows_rsrc(src, ld, rows);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int e = threadIdx.x + q * kThreads;
-        const int r = e >> 4, c = (e & 15) * 4;
-        *(f32x4*)(dst + (int64_t)r * kBb + c) = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
+    for (int q = 0; q < 4; ++q) u[q] = ld4(rs, ((tr + 16 * q) * ld + tc) * 4);
+  };
+  // 64 x 32 product U Xb: wave w has rows 16 w .. 16 w + 15, two 16-column pieces
+  auto product = [&](f32x4 (&acc)[2], const float (*Xb)[kXld]) {
+#pragma unroll
+    for (int k = 0; k < kNb; k += 4) {
+      const float x = U[16 * wave + l16][k + g];
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+        acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, Xb[k + g][16 * p + l16], acc[p], 0, 0, 0);
     }
+  };
+  auto keep = [&](int a, const f32x4 (&acc)[2]) {  // element r: row 4 g + r of the wave's 16
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) Xc[a][16 * wave + 4 * g + r][16 * p + l16] = acc[p][r];
+  };
+
+  const float* D = Dinv + (int64_t)(g0 + b) * kNb * kNb + half * kXw;
+  f32x4 x0[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int e = threadIdx.x + q * kThreads;
+    x0[q] = *(const f32x4*)(D + (e >> 3) * kNb + (e & 7) * 4);
+  }
+  if (b + 1 < n64) issue(b + 1, b);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int e = threadIdx.x + q * kThreads;
+    const int r = e >> 3, c = (e & 7) * 4;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) Xc[b][r][c + j] = x0[q][j];
+    *(f32x4*)(X + (int64_t)(b * kNb + r) * kBb + c) = x0[q];
+  }
+#pragma unroll 1
+  for (int a = b + 1; a < n64; ++a) {
+    f32x4 t[2] = {};
+#pragma unroll 1
+    for (int c = b; c <= a; ++c) {
+      __syncthreads();  // U is read, and the block of X before this product is in LDS
+#pragma unroll
+      for (int q = 0; q < 4; ++q) *(f32x4*)&U[tr + 16 * q][tc] = u[q];
+      if (c == a) keep(a, t);  // T goes through Xc[a]
+      __syncthreads();
+      if (c < a)
+        issue(a, c + 1);
+      else if (a + 1 < n64)
+        issue(a + 1, b);
+      if (c < a) product(t, Xc[c]);
+    }
+    f32x4 x[2] = {};
+    product(x, Xc[a]);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      x[p] = -x[p];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        X[(int64_t)(a * kNb + 16 * wave + 4 * g + r) * kBb + 16 * p + l16] = x[p][r];
+    }
+    __syncthreads();  // every wave has read T
+    keep(a, x);
   }
 }
 
@@ -1454,7 +1423,7 @@ hipError_t launch_solve(const float* G, const float* C, int d, int d_out, float 
   }
   // the inverses X_I of the diagonal blocks, P_I = X_I^T X_I, and Lh_rI = L_rI X_I
   // for the rows below, stored transposed above the diagonal blocks
-  hipLaunchKernelGGL(inv256_kernel, dim3(nb, 4, nl), dim3(kThreads), 0, stream, L, w.dinv, xinv, d, ws);
+  hipLaunchKernelGGL(inv256_kernel, dim3(nb, kBb / kXw, nl), dim3(kThreads), 0, stream, L, w.dinv, xinv, d, ws);
   hipLaunchKernelGGL(xtx_kernel, dim3(10, nb, nl), dim3(kThreads), 0, stream, xinv, pinv, d, ws);
   if (nb > 1) {
     // (m, n) = (column of block I, row below it), for every block that has rows below
