@@ -127,6 +127,9 @@ int ispa_attn_chunk(const void* q, const void* k_cache, const void* v_cache,
  *   workspace  device, 256-byte aligned, at least ispa_attn_workspace_bytes
  *              bytes for the same arguments on the same device; may be NULL
  *              when that is 0. Used only during the call's device work.
+ *              With segments 0, a call of fewer than 384 key tiles or of work
+ *              items that fill the device runs whole where the workspace is
+ *              missing or too small; other calls return ISPA_ERR_INVALID_ARG.
  * Other arguments and outputs as for ispa_attn_chunk.
  */
 int ispa_attn_chunk_ws(const void* q, const void* k_cache, const void* v_cache,

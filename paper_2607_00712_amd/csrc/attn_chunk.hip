@@ -721,6 +721,17 @@ int attn_cu_count() {
 
 namespace {
 
+// The fill of the last round of workgroups as the rule: n_cu runs below 85%
+// (ISPA_ATTN_SPLIT_FILL overrides the percentage, and then decides alone), from
+// 384 tiles on, where the launch is long enough to repay them.
+int64_t fill_segments(int64_t n_work, int T, int n_cu) {
+  const char* env = getenv("ISPA_ATTN_SPLIT_FILL");
+  const int64_t rounds = (n_work + n_cu - 1) / n_cu;
+  if (T < 384 || n_work * 100 >= rounds * n_cu * (env != nullptr ? atoi(env) : 85)) return 0;
+  const int64_t U = n_work * T;
+  return U / n_cu < 16 ? U / 16 : n_cu;
+}
+
 // The automatic split: how many segments (0: whole work items) for n_work items
 // of T tiles each on n_cu compute units, one workgroup on each.
 //
@@ -736,13 +747,9 @@ namespace {
 // 512 597 -> 278 (3), 190 of 512 686 -> 652 (runs), 210 of 147 213 (whole; runs
 // 230), 228 of 512 whole (runs 3% slower); head_dim 64: 168 of 98 145 -> 112
 // (runs), 24 of 74 109 -> 28 (8), 64 of 19 33 -> 26 (4).
-// With more items than compute units the last round's fill decides, from 384
-// tiles on, where the launch is long enough to repay it: runs below 85%.
+// With more items than compute units the last round's fill decides.
 int64_t auto_segments(int64_t n_work, int T, int n_cu, int head_dim, bool dual) {
-  if (n_work > n_cu) {
-    const int64_t rounds = (n_work + n_cu - 1) / n_cu;
-    return T < 384 || n_work * 100 >= rounds * n_cu * 85 ? 0 : n_cu;
-  }
+  if (n_work > n_cu || getenv("ISPA_ATTN_SPLIT_FILL") != nullptr) return fill_segments(n_work, T, n_cu);
   const bool d128 = head_dim == 128;
   const double tile = d128 ? 1.15 : 1.30, full = d128 ? 0.35 : 0.15;  // per tile, and more on a full chip
   const double run_tile = d128 ? 1.65 : 1.50, fixed = d128 ? 8.0 : 6.0, merge = dual ? 12.0 : 7.0;
@@ -779,6 +786,12 @@ bool split_folds(const AttnArgs& a) {
 }
 
 }  // namespace
+
+bool attn_split_optional(const AttnArgs& a) {
+  const int n_cu = attn_cu_count();
+  const int64_t n_work = (int64_t)((a.n_q + kBq - 1) / kBq) * a.n_heads;
+  return n_cu <= 0 || fill_segments(n_work, attn_tiles(a.r, nullptr), n_cu) < 2;
+}
 
 size_t attn_plan_split(const AttnArgs& a, int head_dim, int segments, AttnSplit* s) {
   s->fold = false;

@@ -188,10 +188,14 @@ int ispa_attn_chunk_ws(const void* q, const void* k_cache, const void* v_cache, 
   a.lse_local = lse_local;
   const size_t need = ispa::attn_plan_split(a, head_dim, segments, &a.split);
   if (a.split.n_seg > 0) {
-    if (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < need) return ISPA_ERR_INVALID_ARG;
-    a.split.part_o = (float*)workspace;
-    a.split.part_lse = (float*)((char*)workspace + a.split.lse_offset);
-    a.split.ctr = (uint32_t*)((char*)workspace + a.split.ctr_offset);
+    if (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < need) {
+      if (segments != 0 || !ispa::attn_split_optional(a)) return ISPA_ERR_INVALID_ARG;
+      ispa::attn_plan_split(a, head_dim, -1, &a.split);  // whole work items
+    } else {
+      a.split.part_o = (float*)workspace;
+      a.split.part_lse = (float*)((char*)workspace + a.split.lse_offset);
+      a.split.ctr = (uint32_t*)((char*)workspace + a.split.ctr_offset);
+    }
   }
   return ispa::launch_attn_chunk(a, head_dim, stream) == hipSuccess ? ISPA_OK : ISPA_ERR_HIP;
 }

@@ -78,6 +78,9 @@ int attn_cu_count();
 // items would fill the chip poorly, > 0 forces that many segments. Fills
 // units/n_seg/max_pieces (n_seg = 0: no split) and returns the workspace bytes.
 size_t attn_plan_split(const AttnArgs& a, int head_dim, int segments, AttnSplit* s);
+// Whether an automatic split of this launch may be left out for want of a
+// workspace (a call that fills the last round or is short).
+bool attn_split_optional(const AttnArgs& a);
 hipError_t launch_attn_chunk(const AttnArgs& a, int head_dim, hipStream_t stream);
 // The hand-scheduled head_dim-128 kernel (attn_fast.cpp): whether it takes
 // this launch (its 32-bit work arithmetic fits and its code object loaded on

@@ -311,3 +311,23 @@ def test_14b_chunk_sampled_heads():
         assert_attn(f64(out_l[:, cols])[BLOCK_ROWS], ref["local"][0], f"head {h} local")
         assert_lse(f64(lse[h])[BLOCK_ROWS], ref["full"][1][0], f"head {h} lse")
         assert_lse(f64(lse_l[h])[BLOCK_ROWS], ref["local"][1][0], f"head {h} local lse")
+
+
+@pytest.mark.parametrize("n_q,N,H,d,needed", [(100, 1500, 12, 64, False), (300, 4700, 12, 128, False),
+                                              (256, 32768, 76, 128, True)])
+def test_automatic_split_without_workspace(n_q, N, H, d, needed):
+    # short calls run whole (bit for bit), long ones that leave the device idle are refused
+    q, k, v = synth.chunk_qkv(18, 0, 0, n_q, N, H * d, DEV)
+    out = torch.full((n_q, H * d), float("nan"), device=DEV)
+    lse = torch.empty((H, n_q), device=DEV)
+    stream = torch.cuda.current_stream().cuda_stream
+    st = ispa.lib().ispa_attn_chunk_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), N, N, 0, n_q, H, d, 0.0,
+                                       out.data_ptr(), lse.data_ptr(), None, None, 0, None, 0, stream)
+    torch.cuda.synchronize()
+    if needed:
+        assert st == ispa.ISPA_ERR_INVALID_ARG
+        return
+    assert st == ispa.ISPA_OK
+    whole = ispa.attn_chunk(q, k, v, N, N, H, segments=-1)
+    torch.cuda.synchronize()
+    assert torch.equal(out, whole[0]) and torch.equal(lse, whole[1])
