@@ -17,7 +17,6 @@ works without the library, but every call raises if it is not built.
 """
 
 import ctypes
-import functools
 import os
 
 import torch
@@ -150,9 +149,11 @@ def _require(t, name, dtype, device=None, ndim=2):
         raise ValueError(f"{name} must be a contiguous {ndim}-d tensor")
 
 
-@functools.lru_cache(maxsize=512)
 def _attn_workspace_bytes(index, *sizes):
-    """ispa_attn_workspace_bytes on device `index`: a function of the sizes alone."""
+    """ispa_attn_workspace_bytes on device `index`. Asked for on every call: the plan
+    follows the environment (ISPA_ATTN_SPLIT_FILL) as well as the sizes."""
+    if torch.cuda.current_device() == index:
+        return lib().ispa_attn_workspace_bytes(*sizes)
     with torch.cuda.device(index):
         return lib().ispa_attn_workspace_bytes(*sizes)
 

@@ -331,3 +331,30 @@ def test_automatic_split_without_workspace(n_q, N, H, d, needed):
     whole = ispa.attn_chunk(q, k, v, N, N, H, segments=-1)
     torch.cuda.synchronize()
     assert torch.equal(out, whole[0]) and torch.equal(lse, whole[1])
+
+
+def test_split_fill_override_between_calls(monkeypatch):
+    # the plan follows ISPA_ATTN_SPLIT_FILL as it stands at each call, also for
+    # sizes that were called before: 228 items of 384 tiles run whole by default
+    # (89% of 256 compute units), are split from 95% on, and are whole again
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    n_q, N, H, d = 4680, 24576, 12, 128
+    q, k, v = synth.chunk_qkv(19, 0, 0, n_q, N, H * d, DEV)
+    need = lambda: ispa.lib().ispa_attn_workspace_bytes(N, N, 0, n_q, H, d, 0, 0)
+    monkeypatch.delenv("ISPA_ATTN_SPLIT_FILL", raising=False)
+    whole = ispa.attn_chunk(q, k, v, N, N, H)
+    monkeypatch.setenv("ISPA_ATTN_SPLIT_FILL", "95")
+    if n_cu == 256:
+        assert need() > 0
+    split = ispa.attn_chunk(q, k, v, N, N, H)
+    monkeypatch.delenv("ISPA_ATTN_SPLIT_FILL")
+    if n_cu == 256:
+        assert need() == 0
+    again = ispa.attn_chunk(q, k, v, N, N, H)
+    torch.cuda.synchronize()
+    assert torch.equal(whole[0], again[0]) and torch.equal(whole[1], again[1])
+    # each within ATTN_TOL of the exact result, with its own rounding of the weights
+    assert attn_err(f64(split[0]), f64(whole[0])) <= 2 * ATTN_TOL
+    assert_lse(f64(split[1]), f64(whole[1]), "lse split vs whole")
+    if n_cu == 256:
+        assert not torch.equal(split[0], whole[0])
