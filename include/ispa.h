@@ -154,13 +154,16 @@ size_t ispa_attn_workspace_bytes(int64_t cache_len, int64_t window, int64_t sink
  * life of the process (ISPA_STATIC_SCRATCH_BYTES), instead of a caller
  * workspace; the call itself allocates and frees nothing.
  *   Arguments, outputs and results as for ispa_attn_chunk_ws (bitwise the same
- *   outputs for the same inputs).
+ *   outputs for the same inputs: those of a call with a workspace where the
+ *   split is required, those of a call without one where it may run whole, that
+ *   is with fewer than 384 key tiles or work items that fill the device).
  *   Returns ISPA_ERR_SCRATCH, before enqueueing anything, when the split needs
  *   more than ISPA_STATIC_SCRATCH_BYTES (ispa_attn_workspace_bytes with
  *   segments = 0 tells; a dual-stream chunk of 4680 queries over 7 chunks of
  *   cache that splits, e.g. with 10 heads x 128, needs 129 MiB).
- * Every call on one GPU uses the same array: calls that overlap on one GPU
- * (other streams, other threads) race and give undefined results. The array
+ * Every split call on one GPU uses the same array: split calls that overlap on
+ * one GPU (other streams, other threads) race and give undefined results. Calls
+ * that run whole use no scratch and may overlap with any other. The array
  * needs no clearing: the call clears the counters it uses and writes every
  * partial result before it is read.
  */

@@ -222,9 +222,10 @@ def attn_chunk(q, k_cache, v_cache, cache_len, window, n_heads, sink_len=0, scal
 
 def attn_chunk_noalloc(q, k_cache, v_cache, cache_len, window, n_heads, out, lse, out_local=None, lse_local=None,
                        sink_len=0, scale=0.0):
-    """ispa_attn_chunk_noalloc: attn_chunk with the automatic split, its partial
-    results in the library's fixed per-GPU device scratch. The caller passes the
-    outputs (out_local given: the dual-stream form); nothing is allocated.
+    """ispa_attn_chunk_noalloc: attn_chunk with the automatic split where a call
+    must be split (others run whole), its partial results in the library's fixed
+    per-GPU device scratch. The caller passes the outputs (out_local given: the
+    dual-stream form); nothing is allocated.
     Returns (out, lse[, out_local, lse_local])."""
     L = lib()
     dual = out_local is not None

@@ -147,6 +147,17 @@ int chunk_ranges(int64_t cache_len, int64_t window, int64_t sink_len, int32_t n_
   return ISPA_OK;
 }
 
+// The part of AttnArgs that a split's plan takes; false for invalid sizes.
+bool plan_args(int64_t cache_len, int64_t window, int64_t sink_len, int32_t n_q, int32_t n_heads, int32_t head_dim,
+               bool dual, ispa::AttnArgs* a) {
+  if (head_dim != 64 && head_dim != 128) return false;
+  if (n_q < 1 || n_heads < 1 || n_heads > 65535) return false;
+  memset(a, 0, sizeof(*a));
+  a->n_q = n_q;
+  a->n_heads = n_heads;
+  return chunk_ranges(cache_len, window, sink_len, n_q, dual, &a->r) == ISPA_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -161,13 +172,8 @@ int ispa_attn_chunk(const void* q, const void* k_cache, const void* v_cache, int
 
 size_t ispa_attn_workspace_bytes(int64_t cache_len, int64_t window, int64_t sink_len, int32_t n_q,
                                  int32_t n_heads, int32_t head_dim, int32_t dual, int32_t segments) {
-  if (head_dim != 64 && head_dim != 128) return 0;
-  if (n_q < 1 || n_heads < 1 || n_heads > 65535) return 0;
   ispa::AttnArgs a;
-  memset(&a, 0, sizeof(a));
-  a.n_q = n_q;
-  a.n_heads = n_heads;
-  if (chunk_ranges(cache_len, window, sink_len, n_q, dual != 0, &a.r) != ISPA_OK) return 0;
+  if (!plan_args(cache_len, window, sink_len, n_q, n_heads, head_dim, dual != 0, &a)) return 0;
   ispa::AttnSplit sp;
   return ispa::attn_plan_split(a, head_dim, segments, &sp);
 }
@@ -236,15 +242,21 @@ int ispa_attn_chunk_noalloc(const void* q, const void* k_cache, const void* v_ca
                             int64_t window, int64_t sink_len, int32_t n_q, int32_t n_heads, int32_t head_dim,
                             float scale, float* out, float* lse, float* out_local, float* lse_local,
                             hipStream_t stream) {
-  // The plan of the automatic split; 0 also for invalid arguments, which
-  // ispa_attn_chunk_ws then rejects.
-  const size_t need = ispa_attn_workspace_bytes(cache_len, window, sink_len, n_q, n_heads, head_dim,
-                                                out_local != nullptr, 0);
+  // The plan of the automatic split. Calls that may run whole do: the scratch is
+  // one per GPU, and only calls that use it must not overlap. Invalid arguments
+  // need nothing here and are rejected by ispa_attn_chunk_ws.
+  size_t need = 0;
+  ispa::AttnArgs a;
+  if (plan_args(cache_len, window, sink_len, n_q, n_heads, head_dim, out_local != nullptr, &a) &&
+      !ispa::attn_split_optional(a)) {
+    ispa::AttnSplit sp;
+    need = ispa::attn_plan_split(a, head_dim, 0, &sp);
+  }
   if (need > ISPA_STATIC_SCRATCH_BYTES) return ISPA_ERR_SCRATCH;
   void* ws = nullptr;
   if (need > 0 && (ws = device_scratch()) == nullptr) return ISPA_ERR_HIP;
   return ispa_attn_chunk_ws(q, k_cache, v_cache, cache_len, window, sink_len, n_q, n_heads, head_dim, scale, out,
-                            lse, out_local, lse_local, 0, ws, ISPA_STATIC_SCRATCH_BYTES, stream);
+                            lse, out_local, lse_local, 0, ws, need > 0 ? ISPA_STATIC_SCRATCH_BYTES : 0, stream);
 }
 
 int ispa_attn_ranges(const void* q, const void* k_cache, const void* v_cache, const int64_t* ranges,

@@ -103,3 +103,38 @@ def test_noalloc_rejects_plans_beyond_scratch():
         ispa.attn_chunk_noalloc(q, k, v, N, w, heads, out=outs[0], lse=outs[1], out_local=outs[2],
                                 lse_local=outs[3])
     assert e.value.status == ispa.ISPA_ERR_SCRATCH
+
+
+# calls that the automatic split may leave whole: short ones, and items that fill the device
+OPTIONAL = [(4680, 9360, 9360, 0, 12, 128, False), (300, 4673, 600, 65, 6, 128, True), (1560, 6240, 6240, 0, 24, 64, False)]
+
+
+@pytest.mark.parametrize("case", OPTIONAL)
+def test_noalloc_runs_optional_splits_whole(case):
+    # without the shared scratch, so the outputs are those of whole work items
+    n_q, N, w, sink, heads, hd, dual = case
+    q, k, v = synth.chunk_qkv(20, 0, 0, n_q, N, heads * hd, DEV)
+    outs = _nan_outputs(n_q, heads * hd, heads, dual)
+    assert _call_noalloc(q, k, v, N, w, sink, heads, outs) == ispa.ISPA_OK
+    whole = ispa.attn_chunk(q, k, v, N, w, heads, sink_len=sink, dual=dual, segments=-1)
+    torch.cuda.synchronize()
+    for name, a, b in zip(("out", "lse", "out_local", "lse_local"), outs, whole):
+        assert torch.equal(a, b), f"{name}: not the whole call's"
+
+
+def test_noalloc_optional_splits_overlap():
+    # such calls use no scratch, so those of two streams may overlap
+    n_q, N, heads, hd = 300, 4673, 12, 128
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    sets = [synth.chunk_qkv(21, i, 0, n_q, N, heads * hd, DEV) for i in range(2)]
+    refs = [ispa.attn_chunk(*x, N, N, heads, segments=-1) for x in sets]
+    outs = [[_nan_outputs(n_q, heads * hd, heads, False) for _ in range(8)] for _ in sets]
+    torch.cuda.synchronize()
+    for i in range(8):
+        for st, x, o in zip(streams, sets, outs):
+            with torch.cuda.stream(st):
+                assert _call_noalloc(*x, N, N, 0, heads, o[i]) == ispa.ISPA_OK
+    torch.cuda.synchronize()
+    for ref, per_stream in zip(refs, outs):
+        for o in per_stream:
+            assert torch.equal(o[0], ref[0]) and torch.equal(o[1], ref[1])
