@@ -271,7 +271,8 @@ int ispa_accum_stats(ispa_stats* handle, const void* x, int32_t x_dtype,
  *   eps_out   host double or NULL: the feasibility score of Eq. 6,
  *             ||X dW - R||_F^2 = s - <dW, C> - lambda ||dW||_F^2
  * G and C are left unchanged, so the caller may solve again with another
- * lambda or keep accumulating. Waits for the handle's stream to finish; returns
+ * lambda or keep accumulating. A column of C with an infinity or a NaN gives a
+ * column of NaN in delta_w and leaves the others as they are. Waits for the handle's stream to finish; returns
  * ISPA_ERR_NOT_SPD (delta_w then unspecified) if a pivot is not positive.
  * From d_in = 4096 on (with d_out >= 128) the triangular solves of half of
  * C's columns run on a second stream that the library owns (one per device);

@@ -908,9 +908,16 @@ namespace {
 //
 // The descriptor of a side ends at its last valid element, so k past K reads
 // zero where k is the source's row and is masked where k is the column; rows and
-// columns past M or N only reach outputs that are not stored. The order of an
-// output's sum does not depend on the tile size: both give the same bits. An
-// infinite value, or one that rounds to an infinite bf16, gives NaN.
+// columns past M or N read zero. The order of an output's sum does not depend on
+// the tile size: both give the same bits.
+//
+// bf16 has fp32's exponents, but the lower parts of a value need up to 16 more
+// below: from 2^-110 down they lose bits (at 2^-126 a value would keep 8 of 24), and
+// the largest fp32 values round to an infinite bf16. Tiles that hold such values,
+// or whose sums leave fp32's range, are computed a second time with each row of both
+// sides scaled by a power of two of its own. The test costs an or per pair of
+// values and a barrier at the end (0.1-0.6% of a solve; scaling every operand up
+// front 1.7-3%). An infinite or NaN value gives NaN.
 struct SplitJob {
   const float* A;
   float* C;
@@ -942,6 +949,7 @@ struct SplitSide {
   __amdgpu_buffer_rsrc_t rs;
   int voff[KM ? 8 : 1], step, k_first, dst;
   float v[8];
+  u32 seen = 0;  // the first parts put so far, or-ed
 
   // byte of chunk c of row r in a plane: a 16-lane group of an operand read
   // (16 rows, one chunk) covers all banks once
@@ -960,7 +968,8 @@ struct SplitSide {
     dst = slot(row, chunk);
     if (KM) {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) voff[k % (KM ? 8 : 1)] = (k_first + k) * ld4 + row * 4;
+      for (int k = 0; k < 8; ++k)
+        voff[k % (KM ? 8 : 1)] = row < iend - i0 ? (k_first + k) * ld4 + row * 4 : kNoCol;
       step = kKs * ld4;
     } else {
       voff[0] = row * ld4 + k_first * 4;
@@ -988,11 +997,41 @@ struct SplitSide {
     for (int k = 0; k < 8; ++k)
       if (k0 + k_first + k >= K) v[k] = 0.f;
   }
-  __device__ __forceinline__ void put(char* lds) const {
+  __device__ __forceinline__ void put(char* lds) {
     u32x4 p[3];
     split8(v, p);
+    seen |= p[0][0] | p[0][1] | p[0][2] | p[0][3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) *(u32x4*)(lds + q * (kBytes / 3) + dst) = p[q];
+  }
+  // every value put so far is below 2^-95, and not all are zero: a value below
+  // 2^-110 beside a larger one loses at most 2^-39 of that one
+  __device__ __forceinline__ bool tiny() const {
+    const u32 exps = (seen | seen >> 16) & 0x7fff;
+    return exps != 0 && (exps & 0x7000) == 0;
+  }
+  __device__ __forceinline__ float top() const {
+    float m = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) m = fmaxf(m, fabsf(v[k]));
+    return m;
+  }
+  __device__ __forceinline__ void scale(float by) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] *= by;
+  }
+  // The power of two that brings the row's largest magnitude (top: of this thread's
+  // chunk) to 2^50, so that sums of 2^9 products of two sides stay finite; the
+  // rows' exponents go to exps. red: T x kChunks floats of LDS.
+  __device__ __forceinline__ float row_scale(float top, float* red, int* exps) const {
+    const int t = threadIdx.x;
+    const int row = KM ? t % T : t / kChunks, chunk = KM ? t / T : t % kChunks;
+    red[row * kChunks + chunk] = top;
+    __syncthreads();
+    for (int c = 0; c < kChunks; ++c) top = fmaxf(top, red[row * kChunks + c]);
+    const int e = min(50 + 127 - (int)(__builtin_bit_cast(u32, top) >> 23), 64);
+    exps[row] = e;
+    return __builtin_amdgcn_ldexpf(1.f, e);
   }
 };
 
@@ -1003,6 +1042,7 @@ __global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(Sp
   using SideB = SplitSide<T, B_KM>;
   constexpr int kKs = SideA::kKs, kSide = SideA::kBytes;
   __shared__ __attribute__((aligned(1024))) char smem[2][2 * kSide];
+  __shared__ int exps[2][T], again;
   // consecutive tiles (n fastest, then m, job or block, layer) on one XCD
   const int idx = (int)(blockIdx.x & 7) * ((int)gridDim.x >> 3) + (int)(blockIdx.x >> 3);
   auto tiles = [](int n) { return n > 0 ? (n + T - 1) / T : 0; };
@@ -1067,6 +1107,7 @@ __global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(Sp
       sb.mask(s * kKs, K);
     }
   };
+  if (threadIdx.x == 0) again = 0;
   sa.load(s0);
   sb.load(s0);
   mask(s0);
@@ -1139,6 +1180,56 @@ __global__ __launch_bounds__(kThreads, Q == 2 ? 2 : 3) void gemm_split_kernel(Sp
       }
       __syncthreads();
     }
+  }
+
+  // Where a value or a sum left bf16's or fp32's range, or a thread's values were
+  // all so small that their lower parts may have, the tile is computed again with
+  // every row of both sides scaled by a power of two of its own.
+  float odd = 0.f;  // NaN where a sum is not finite
+#pragma unroll
+  for (int i = 0; i < Q; ++i)
+#pragma unroll
+    for (int j = 0; j < Q; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) odd = fmaf(acc[i][j][r], 0.f, odd);
+  if (odd != 0.f || sa.tiny() || sb.tiny()) again = 1;
+  __syncthreads();  // also: every wave has read the last stage
+  if (__builtin_amdgcn_readfirstlane(again) != 0) {
+    float ta = 0.f, tb = 0.f;
+    for (int u = s0; u < steps; ++u) {
+      sa.load(u);
+      sb.load(u);
+      mask(u);
+      ta = fmaxf(ta, sa.top());
+      tb = fmaxf(tb, sb.top());
+    }
+    const float ua = sa.row_scale(ta, (float*)smem[0], exps[0]);
+    const float ub = sb.row_scale(tb, (float*)smem[1], exps[1]);
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+#pragma unroll
+      for (int j = 0; j < Q; ++j) acc[i][j] = f32x16{};
+#pragma unroll 1
+    for (int u = s0; u < steps; ++u) {
+      sa.load(u);
+      sb.load(u);
+      mask(u);
+      sa.scale(ua);
+      sb.scale(ub);
+      __syncthreads();
+      sa.put(smem[0]);
+      sb.put(smem[0] + kSide);
+      __syncthreads();
+      products(smem[0]);
+    }
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+#pragma unroll
+      for (int j = 0; j < Q; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          acc[i][j][r] = __builtin_amdgcn_ldexpf(
+              acc[i][j][r], -(exps[0][wm0 + 32 * i + acc_row(r, lane)] + exps[1][wn0 + 32 * j + l32]));
   }
 
 #pragma unroll

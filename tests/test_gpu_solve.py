@@ -453,3 +453,76 @@ def test_eps_small_relative_to_s():
     assert eps_ref == pytest.approx(oracle.feasibility_direct(f64(x), r, dw_ref), rel=1e-6)
     assert 1e-4 < eps_ref / ref.s < 1e-2
     assert abs(eps - eps_ref) <= 0.02 * eps_ref, (eps, eps_ref, ref.s)
+
+
+def _range_problem(st, d, d_out, n, wid):
+    x = rows(wid, 0, n, d)
+    y = synth.normal((n, d_out), synth.seed_of(wid, 0, synth.Y_FULL), DEV, dtype=torch.float32)
+    st.accum(x, y, torch.zeros_like(y))
+    return st.views()[:2]
+
+
+# a single layer (64 x 64 tiles) and enough layers for the sweeps' 128 x 128 tiles
+RANGE_SIZES = [(264, 72, 1), (520, 136, 40)]
+
+
+@pytest.mark.parametrize("d,d_out,layers", RANGE_SIZES)
+def test_solve_column_scales(d, d_out, layers):
+    # dW = (G + lambda I)^-1 C column by column, and fp32 holds each to its own
+    # scale: columns of C scaled by powers of two give dW's columns scaled alike,
+    # from dW of 2^-118 up to a C that reaches the largest finite fp32 value, next
+    # to each other in one tile. The entries of dW below 2^-126 are rounded to
+    # 2^-150, under 2^-24 of their column here; all else is exact.
+    lam, n = 0.5, 2 * d
+    sb = ispa.StatsBatch(layers, d, d_out, max_rows=n, device=DEV)
+    for i, st in enumerate(sb.layers):
+        _range_problem(st, d, d_out, n, 50 + i)
+    ref = [sb.layers[i].solve_async(lam)[0].double() for i in (0, layers - 1)]
+    k = torch.zeros(d_out, dtype=torch.int32, device=DEV)
+    k[1::4], k[2::4], k[3::4] = -112, 60, 115  # C of about 2^5: dW of 2^-118, ..., C of 2^120
+    for st in sb.layers:
+        C = st.views()[1]
+        C.copy_(torch.ldexp(C, k))
+    # column 0 of the first layer: one entry, the largest fp32 value, which bf16
+    # rounds to infinity
+    C = sb.layers[0].views()[1]
+    C[:, 0] = 0
+    C[3, 0] = 1.0
+    unit = sb.layers[0].solve_async(lam)[0][:, 0].double()
+    top = C[3, 0] = torch.finfo(torch.float32).max
+    # an infinity and a NaN spoil their own columns alone
+    C[5, 4], C[6, 8] = float("inf"), float("nan")
+    dw, _, status = sb.solve(lam)
+    torch.cuda.synchronize()
+    assert status.tolist() == [0] * layers
+    spoilt = torch.isnan(dw)
+    assert spoilt[0, :, [4, 8]].all() and int(spoilt.sum()) == 2 * d and not torch.isinf(dw).any()
+    dw[0, :, [4, 8]] = ref[0][:, [4, 8]].float()
+    for i, r in zip((0, layers - 1), ref):
+        want = torch.ldexp(r, k)[:, 1:]
+        err = (dw[i][:, 1:].double() - want).norm(dim=0) / want.norm(dim=0)
+        assert float(err.max()) <= 2.0 ** -22, (i, err)
+    # top is not a power of two: the rounding of an fp32 solve
+    assert float((dw[0][:, 0].double() - unit * top).norm() / (unit * top).norm()) <= 1e-5
+
+
+@pytest.mark.parametrize("d,d_out,layers", RANGE_SIZES)
+@pytest.mark.parametrize("k", [112, -112])
+def test_solve_system_scales(d, d_out, layers, k):
+    # G, lambda and C scaled by one power of two leave dW unchanged: its inverse
+    # blocks then hold values of 2^-120 or 2^105, whose products and smaller entries
+    # below 2^-126 are rounded to 2^-150 (4e-7 to 5e-7 of dW, with fp32 products 5e-7)
+    lam, n = 0.5, 2 * d
+    sb = ispa.StatsBatch(layers, d, d_out, max_rows=n, device=DEV)
+    for i, st in enumerate(sb.layers):
+        _range_problem(st, d, d_out, n, 50 + i)
+    want = sb.solve(lam)[0].double()
+    for st in sb.layers:
+        G, C = st.views()[:2]
+        G.copy_(torch.ldexp(G, torch.tensor(k, device=DEV)))
+        C.copy_(torch.ldexp(C, torch.tensor(k, device=DEV)))
+    dw, _, status = sb.solve(float(np.ldexp(lam, k)))
+    torch.cuda.synchronize()
+    assert status.tolist() == [0] * layers
+    err = (dw.double() - want).norm(dim=(1, 2)) / want.norm(dim=(1, 2))
+    assert float(err.max()) <= 2.0 ** -20, err
