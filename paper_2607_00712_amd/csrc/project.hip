@@ -283,19 +283,44 @@ __global__ __launch_bounds__(kPThreads) __attribute__((amdgpu_waves_per_eu(2))) 
   }
 }
 
+// The largest m of the wave's lanes: over rows of 16 by DPP, then four scalars (a
+// shuffle through LDS takes about 100 cycles for each of six steps).
+__device__ __forceinline__ float wave_max(float m) {
+  auto dpp = [](float v, auto ctrl) {
+    return __uint_as_float(
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  m = fmaxf(m, dpp(m, std::integral_constant<int, 0xb1>()));   // lane ^ 1
+  m = fmaxf(m, dpp(m, std::integral_constant<int, 0x4e>()));   // lane ^ 2
+  m = fmaxf(m, dpp(m, std::integral_constant<int, 0x141>()));  // mirrored within 8
+  m = fmaxf(m, dpp(m, std::integral_constant<int, 0x140>()));  // mirrored within 16
+  float r[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    r[i] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(m), 16 * i));
+  return fmaxf(fmaxf(r[0], r[1]), fmaxf(r[2], r[3]));
+}
+
 // Codes and scale of one row per wave, 8 values per lane and chunk of 512 columns
 // (cols a multiple of 8, rows 16-byte aligned). The first NK chunks are loaded
-// at once and stay in registers between the absmax and the codes; later ones are
-// read again. Chunks are buffers that end with the row: no branch around a load.
+// at once and stay in registers between the absmax and the codes; the later ones
+// of rows wider than kMost chunks are read again, kTail at a time. Chunks are
+// buffers that end with the row: no branch around a load.
 // A code is rint(x / s) with the quotient rounded to fp32. The product with 1 / s
-// is within 127 x 2^-22 of the quotient, so its rounding is the code unless it
-// lies within 1e-4 of a half (or is not a number): then the chunk is divided.
-// 4680 x 1536 bf16: 8.0 us, 8.6 with a second read and a division per value; the
-// rest is the launch and the memory's latency (21.6 MB).
+// is within 127 x 2^-22 of the quotient, so its rounding (by adding 1.5 x 2^23, the
+// code then in the low byte) is the code unless it lies within 1e-4 of a half (or
+// is not a number): then the chunk is divided. Rows of one chunk are divided right
+// away and loaded without a descriptor: the reciprocal and the descriptor would only
+// lengthen their chain (18720 x 512 bf16: 8.0 us, 9.5 with both).
+// Bound by the launch and the memory's latency up to 21 MB (4680 x 1536 bf16 6.7 us;
+// 6.9 with a second read and a division per value), then by the memory: 18720 x
+// 5120 bf16 47 us, 6.1 TB/s of reads and writes (74).
+constexpr int kMost = 10;
 template <typename T, int NK>
 __global__ __launch_bounds__(256) void quant_rows_kernel(const T* __restrict__ x, int64_t rows, int cols,
                                                          int8_t* __restrict__ q, float* __restrict__ scale) {
   constexpr int kWide = sizeof(T) == 2 ? 1 : 2;  // 16-byte pieces per chunk and lane
+  constexpr int kTail = 4;  // later chunks loaded at once
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (row >= rows) return;
@@ -305,6 +330,13 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const T* __restrict__ x
     return (int)(left < 0 ? 0 : left < 512 ? left : 512);
   };
   auto load = [&](int chunk, u32x4 (&u)[kWide]) {
+    if constexpr (NK == 1) {
+      const u32x4* p = (const u32x4*)(x + row * cols + lane * 8);
+      const bool in = lane * 8 < cols;
+#pragma unroll
+      for (int w = 0; w < kWide; ++w) u[w] = in ? p[w] : u32x4{0, 0, 0, 0};
+      return;
+    }
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<T*>(x + row * cols + (int64_t)chunk * 512), 0, inside(chunk) * (int)sizeof(T), 0x00020000);
 #pragma unroll
@@ -327,30 +359,36 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const T* __restrict__ x
   };
 #pragma unroll
   for (int k = 0; k < NK; ++k) top(kept[k]);
-  for (int k = NK; k < chunks; ++k) {
-    u32x4 u[kWide];
-    load(k, u);
-    top(u);
-  }
+  for (int k = NK; NK == kMost && k < chunks; k += kTail) {
+    u32x4 u[kTail][kWide];
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    for (int j = 0; j < kTail; ++j) load(k + j, u[j]);
+#pragma unroll
+    for (int j = 0; j < kTail; ++j) top(u[j]);
+  }
+  m = wave_max(m);
   const float s = m > 0.0f ? m / 127.0f : 1.0f;
   const float inv = 1.0f / s;
   if (lane == 0) scale[row] = s;
-  auto codes = [&](const u32x4 (&u)[kWide], int chunk) {
-    u32x2 out = {0, 0};
-    bool near = false;  // a product too near a half to round
+  auto codes = [&](const u32x4 (&raw)[kWide], int chunk) {
+    bool near = NK == 1;  // a product too near a half to round
+    uint32_t u[8] = {};   // 1.5 x 2^23 + code: the code in the low byte
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float t = value(u, e) * inv, r = rintf(t);
-      near |= !(fabsf(t - r) <= 0.4999f);
-      out[e / 4] |= ((uint32_t)(int)fminf(fmaxf(r, -127.0f), 127.0f) & 0xffu) << (8 * (e % 4));
+    for (int e = 0; NK > 1 && e < 8; ++e) {
+      const float x = value(raw, e), t = fmaf(x, inv, 12582912.0f);
+      near |= !(fabsf(fmaf(x, inv, 12582912.0f - t)) <= 0.4999f);
+      u[e] = __float_as_uint(t);
     }
+    u32x2 out;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      out[h] = __builtin_amdgcn_perm(u[4 * h + 1], u[4 * h], 0x0c0c0400u) |
+               __builtin_amdgcn_perm(u[4 * h + 3], u[4 * h + 2], 0x04000c0cu);
     if (near) {
       out = u32x2{0, 0};
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float r = fminf(fmaxf(rintf(value(u, e) / s), -127.0f), 127.0f);
+        const float r = fminf(fmaxf(rintf(value(raw, e) / s), -127.0f), 127.0f);
         out[e / 4] |= ((uint32_t)(int)r & 0xffu) << (8 * (e % 4));
       }
     }
@@ -361,10 +399,13 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const T* __restrict__ x
 #pragma unroll
   for (int k = 0; k < NK; ++k)
     if (k < chunks) codes(kept[k], k);
-  for (int k = NK; k < chunks; ++k) {
-    u32x4 u[kWide];
-    load(k, u);
-    codes(u, k);
+  for (int k = NK; NK == kMost && k < chunks; k += kTail) {
+    u32x4 u[kTail][kWide];
+#pragma unroll
+    for (int j = 0; j < kTail; ++j) load(k + j, u[j]);
+#pragma unroll
+    for (int j = 0; j < kTail; ++j)
+      if (k + j < chunks) codes(u[j], k + j);
   }
 }
 
@@ -437,21 +478,25 @@ hipError_t launch_project_w8a8(const int8_t* qa, const float* sa, const int8_t* 
 hipError_t launch_quantize_rows(const void* x, int x_bf16, int64_t rows, int cols, int8_t* q, float* scale,
                                 hipStream_t stream) {
   const unsigned grid = (unsigned)((rows + 3) / 4);
-  // chunks kept in registers: 3 (widths to 1536), else 10 (to 5120; wider rows
-  // read the rest twice)
-  if (x_bf16 && cols <= 1536) {
-    hipLaunchKernelGGL((quant_rows_kernel<uint16_t, 3>), dim3(grid), dim3(256), 0, stream, (const uint16_t*)x, rows,
-                       cols, q, scale);
-  } else if (x_bf16) {
-    hipLaunchKernelGGL((quant_rows_kernel<uint16_t, 10>), dim3(grid), dim3(256), 0, stream, (const uint16_t*)x, rows,
-                       cols, q, scale);
-  } else if (cols <= 1536) {
-    hipLaunchKernelGGL((quant_rows_kernel<float, 3>), dim3(grid), dim3(256), 0, stream, (const float*)x, rows, cols, q,
-                       scale);
-  } else {
-    hipLaunchKernelGGL((quant_rows_kernel<float, 10>), dim3(grid), dim3(256), 0, stream, (const float*)x, rows, cols,
-                       q, scale);
-  }
+  // as many chunks as the row has, rounded up to a form: chunks past the row cost
+  // their issue (4680 x 1544 bf16, four chunks: 7.0 us, 8.65 with ten) and registers
+  // cost wavefronts (8 per SIMD up to 6 chunks, 4 at ten)
+  const int chunks = (cols + 511) / 512;
+  auto launch = [&](auto nk) {
+    constexpr int NK = decltype(nk)::value;
+    if (x_bf16)
+      hipLaunchKernelGGL((quant_rows_kernel<uint16_t, NK>), dim3(grid), dim3(256), 0, stream, (const uint16_t*)x, rows,
+                         cols, q, scale);
+    else
+      hipLaunchKernelGGL((quant_rows_kernel<float, NK>), dim3(grid), dim3(256), 0, stream, (const float*)x, rows, cols,
+                         q, scale);
+  };
+  if (chunks <= 1) launch(std::integral_constant<int, 1>());
+  else if (chunks <= 2) launch(std::integral_constant<int, 2>());
+  else if (chunks <= 3) launch(std::integral_constant<int, 3>());
+  else if (chunks <= 4) launch(std::integral_constant<int, 4>());
+  else if (chunks <= 6) launch(std::integral_constant<int, 6>());
+  else launch(std::integral_constant<int, kMost>());
   return hipGetLastError();
 }
 

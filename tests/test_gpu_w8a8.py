@@ -69,6 +69,26 @@ def test_quantize_rows_register_edges(dtype, cols):
     assert np.array_equal(s.cpu().numpy().view(np.int32), want_s.view(np.int32))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("cols", [8, 1016, 1024, 1032, 2040, 2048, 2056, 3064, 3072, 3080, 5120, 7160, 7168, 7176])
+def test_quantize_rows_chunk_forms(dtype, cols):
+    # widths at the ends of every form of the kernel (1, 2, 3, 4, 6 and 10 chunks
+    # kept) and of the groups of chunks read again, with the absmax in each lane's
+    # place of the reduction in turn, and rows whose scale is subnormal, whose
+    # reciprocal is infinite, or that reach the type's largest value
+    rows = 70
+    x = rows_input(rows, cols, dtype, cols).float()
+    r = torch.arange(3, rows)
+    x[r, (8 * (r - 3)) % cols] = 3.0 * x[3:].abs().amax(dim=1)
+    x[3:6] = x[3:6] / x[3:6].abs().amax(dim=1, keepdim=True) * torch.tensor([[1e-39], [3e-37], [3.3e38]])
+    x = x.to(dtype)
+    q, s = ispa.quantize_rows(x.to(DEV))
+    torch.cuda.synchronize()
+    want_q, want_s = oracle.quantize_rows(x.float().numpy())
+    assert np.array_equal(q.cpu().numpy(), want_q)
+    assert np.array_equal(s.cpu().numpy().view(np.int32), want_s.view(np.int32))
+
+
 def codes(rows, cols, g):
     return torch.randint(-127, 128, (rows, cols), generator=g, dtype=torch.int8)
 
