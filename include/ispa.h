@@ -108,16 +108,17 @@ int ispa_attn_chunk(const void* q, const void* k_cache, const void* v_cache,
 /*
  * ispa_attn_chunk with the work split over the whole chip. Whole work items
  * (256 queries of one head over all their keys) per workgroup can leave a
- * large part of the last round of workgroups idle (e.g. 12 heads x 19 query
- * blocks = 228 work items on 256 compute units). Split, every workgroup takes
+ * large part of the last round of workgroups idle (e.g. 10 heads x 19 query
+ * blocks = 190 work items on 256 compute units). Split, every workgroup takes
  * an equal run of (work item, 64-key tile) units; runs that end inside a work
  * item leave a normalised partial output and LSE in the workspace, combined
  * with Eq. 11-12 in run order, by a merge kernel after the launch or, at
  * head_dim 128 where that is faster, by the run that completes a work item (the
  * runs count themselves on per-item counters in the workspace, which the call
  * clears first). The results agree with ispa_attn_chunk within rounding (the
- * merge reassociates the softmax sums) and do not depend on which run finishes
- * last.
+ * merge reassociates the softmax sums, and a run's weights are rounded to bf16
+ * against the run's own largest score: about 2e-3 of the result, as far as either
+ * is from the exact one) and do not depend on which run finishes last.
  *
  *   segments   < 0: never split (exactly ispa_attn_chunk)
  *              0:   split when whole work items would fill the device poorly

@@ -740,13 +740,14 @@ int64_t fill_segments(int64_t n_work, int T, int n_cu) {
 // at once; n_cu equal runs over item boundaries. A tile costs more the fuller
 // the chip is (its power limit) and more in runs (they walk a head's keys at two
 // offsets, which the L2 bridges less well); pieces pay the partial results'
-// traffic and the merge kernel. Fitted to, and choosing as, sweeps of items,
-// tiles and pieces (measured whole -> chosen, us): head_dim 128: 84 items of 147
-// tiles 181 -> 101 (3 pieces), 84 of 25 41 -> 41 (whole), 60 of 47 66 -> 43 (4),
-// 12 of 74 95 -> 32 (12), 4 of 32 46 -> 23 (8), 1 of 512 588 -> 42 (32), 76 of
-// 512 597 -> 278 (3), 190 of 512 686 -> 652 (runs), 210 of 147 213 (whole; runs
-// 230), 228 of 512 whole (runs 3% slower); head_dim 64: 168 of 98 145 -> 112
-// (runs), 24 of 74 109 -> 28 (8), 64 of 19 33 -> 26 (4).
+// traffic and the merge kernel. Fitted to sweeps of items, tiles and pieces on 256
+// compute units, where its choices are within 4% of the best piece count (measured
+// whole -> chosen, us): head_dim 128: 84 items of 147 tiles 185 -> 109 (3 pieces),
+// 84 of 25 42 (whole; 41 in 3), 60 of 47 66 -> 46 (4; 45 in 3), 12 of 74 94 -> 33
+// (11), 4 of 32 47 -> 24 (8), 1 of 512 588 -> 44 (32), 76 of 512 600 -> 288 (3),
+// 190 of 512 701 -> 668 (runs), 210 of 147 226 (whole; runs 237), 228 of 512 805
+// (whole; runs 805 with 1.7 times the traffic); head_dim 64: 168 of 98 144 -> 116
+// (runs), 24 of 74 108 -> 28 (10), 64 of 19 33 -> 27 (4).
 // With more items than compute units the last round's fill decides.
 int64_t auto_segments(int64_t n_work, int T, int n_cu, int head_dim, bool dual) {
   if (n_work > n_cu || getenv("ISPA_ATTN_SPLIT_FILL") != nullptr) return fill_segments(n_work, T, n_cu);

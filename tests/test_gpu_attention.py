@@ -358,3 +358,24 @@ def test_split_fill_override_between_calls(monkeypatch):
     assert_lse(f64(split[1]), f64(whole[1]), "lse split vs whole")
     if n_cu == 256:
         assert not torch.equal(split[0], whole[0])
+
+
+@pytest.mark.parametrize("d,blocks,H,T,segments", [
+    # 256-query blocks, heads, 64-key tiles -> runs of the automatic split (0: whole items)
+    (128, 7, 12, 147, 3 * 84), (128, 7, 12, 25, 0), (128, 5, 12, 47, 4 * 60), (128, 1, 12, 74, 11 * 12),
+    (128, 1, 4, 32, 8 * 4), (128, 1, 1, 512, 32), (128, 19, 4, 512, 3 * 76), (128, 19, 10, 512, 256),
+    (128, 15, 14, 147, 0), (128, 19, 12, 512, 0),
+    (64, 7, 24, 98, 256), (64, 1, 24, 74, 10 * 24), (64, 4, 16, 19, 4 * 64),
+])
+def test_automatic_split_plans(d, blocks, H, T, segments):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("plans for 256 compute units")
+    n_q, N = min(256 * blocks, 64 * T), 64 * T
+    L = ispa.lib()
+    auto = L.ispa_attn_workspace_bytes(N, N, 0, n_q, H, d, 0, 0)
+    if segments == 0:
+        assert auto == 0
+        return
+    assert auto == L.ispa_attn_workspace_bytes(N, N, 0, n_q, H, d, 0, segments)
+    for near in (segments - blocks * H, segments + blocks * H):  # a piece fewer or more per item
+        assert auto != L.ispa_attn_workspace_bytes(N, N, 0, n_q, H, d, 0, near)
