@@ -481,7 +481,7 @@ hipError_t launch_quantize_rows(const void* x, int x_bf16, int64_t rows, int col
   // as many chunks as the row has, rounded up to a form: chunks past the row cost
   // their issue (4680 x 1544 bf16, four chunks: 7.0 us, 8.65 with ten) and registers
   // cost wavefronts (8 per SIMD up to 6 chunks, 4 at ten)
-  const int chunks = (cols + 511) / 512;
+  const int chunks = (int)(((int64_t)cols + 511) / 512);
   auto launch = [&](auto nk) {
     constexpr int NK = decltype(nk)::value;
     if (x_bf16)

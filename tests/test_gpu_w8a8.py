@@ -89,6 +89,21 @@ def test_quantize_rows_chunk_forms(dtype, cols):
     assert np.array_equal(s.cpu().numpy().view(np.int32), want_s.view(np.int32))
 
 
+def test_quantize_rows_widest():
+    # the widest row that 32 bits of columns allow: the absmax and other values
+    # far behind the chunks kept in registers, the count of chunks beyond 32 bits
+    # of columns plus a chunk
+    cols = 2 ** 31 - 8
+    x = torch.zeros((1, cols), dtype=torch.bfloat16, device=DEV)
+    at = torch.tensor([0, 511, 512, 5120, 2 ** 30 + 1, cols - 513, cols - 1], device=DEV)
+    x[0, at] = torch.tensor([3.0, -5.0, 7.0, -11.0, 13.0, -17.0, 127.0], dtype=torch.bfloat16, device=DEV)
+    q, s = ispa.quantize_rows(x)
+    torch.cuda.synchronize()
+    assert s.item() == 1.0
+    assert q[0, at].tolist() == [3, -5, 7, -11, 13, -17, 127]
+    assert torch.count_nonzero(q).item() == len(at)
+
+
 def codes(rows, cols, g):
     return torch.randint(-127, 128, (rows, cols), generator=g, dtype=torch.int8)
 
