@@ -63,11 +63,11 @@ PEAK_HBM_GBS = 8000.0
 # HBM bytes of one dual-stream attention call (one launch of the attention
 # kernel; neither shape splits its work items), from rocprofv3 FETCH_SIZE and WRITE_SIZE
 # scaled by the plain-copy calibration (profiles/attn_fast_wan13b_dual.md,
-# profiles/hbm_copy_calibration.md). Valid only for the kernel source they were
-# taken on; reported as null otherwise.
+# profiles/attn_fast_14b_dual.md, profiles/hbm_copy_calibration.md). Valid only
+# for the kernel source they were taken on; reported as null otherwise.
 MEASURED_TRAFFIC = {
-    "1.3b": {"attn_chunk_sha256_16": "19a83339c0ca5e14", "bytes_per_launch": 391.7e6},
-    "14b": {"attn_chunk_sha256_16": "19a83339c0ca5e14", "bytes_per_launch": 3059.9e6},
+    "1.3b": {"attn_chunk_sha256_16": "d492607c71f9e7e7", "bytes_per_launch": 391.7e6},
+    "14b": {"attn_chunk_sha256_16": "d492607c71f9e7e7", "bytes_per_launch": 3060.0e6},
 }
 
 
@@ -790,7 +790,7 @@ def main():
         },
         "roofline": {
             "kernel": "ispa_attn_fast_d128 (F-Layer, dual stream; one launch per call, whole work items: "
-                      "228 of them fill 89% of the chip, which at its power limit runs them as fast as split)",
+                      f"{w['heads'] * ((w['n_q'] + 255) // 256)} of them on 256 compute units)",
             "bound": "mfma",
             "achieved": round(achieved, 2),
             "peak": PEAK_BF16_TFLOPS,
